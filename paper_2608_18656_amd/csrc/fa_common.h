@@ -147,6 +147,33 @@ __device__ __forceinline__ half8_t cat_half8(short4_t lo, short4_t hi) {
     return __builtin_bit_cast(half8_t, s);
 }
 
+// Address of an LDS object.
+__device__ __forceinline__ unsigned lds_address(void *p) {
+    typedef __attribute__((address_space(3))) char lds_char;
+    return (unsigned)(unsigned long long)(lds_char *)p;
+}
+
+// 16 bytes per lane from a buffer view (its base address and size in bytes)
+// straight into LDS: lane l's bytes land at LDS address dst + 16 l (dst the same
+// for the wave); lanes past the end of the view write zeros (checked on gfx950).  In
+// assembly, with no result register, because the compiler makes every later
+// LDS read wait for such loads; nothing waits for them but lds_loads_done(),
+// which goes before the barrier that publishes the data.  base, bytes and dst
+// are wave-uniform; the s_nop covers a scalar register that a vector
+// instruction wrote just before (five wait states to its use in an address).
+__device__ __forceinline__ void load_lds16(const void *base, int bytes, unsigned dst, int off) {
+    const unsigned long long p = (unsigned long long)base;   // below 2^48: the descriptor's stride bits stay 0
+    const uint4_t rsrc = {(unsigned)p, (unsigned)(p >> 32), (unsigned)bytes, 0x00020000u};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
+                 : "memory");
+}
+template <int N> __device__ __forceinline__ void lds_loads_done() {   // all but the last N loads of the wave
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Workgroup barrier for LDS alone: the wave's own LDS accesses are done, its
+// loads from memory stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Global 16-byte load / store helpers.
 __device__ __forceinline__ uint4_t ld16(const void *p) {
     return *reinterpret_cast<const uint4_t *>(p);
@@ -156,5 +183,21 @@ __device__ __forceinline__ void st16(void *p, uint4_t v) { *reinterpret_cast<uin
 __device__ __forceinline__ uint4_t ld16_stream(const void *p) {
     return __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(p));
 }
+
+// Division of n < 2^31 by a launch constant d >= 1 in three scalar
+// instructions (an integer division takes some twenty vector ones, which
+// delay a kernel's first loads): with 2^(s-1) < d <= 2^s and m =
+// ceil(2^(31+s) / d), floor(n / d) = floor(n m / 2^(31+s)), since n (m d -
+// 2^(31+s)) < 2^31 d <= 2^(31+s).
+struct Divisor {
+    unsigned d, m, shift;
+    explicit Divisor(unsigned div = 1) : d(div) {
+        unsigned s = 0;
+        while ((1ull << s) < d) ++s;
+        shift = 31 + s;
+        m = (unsigned)(((1ull << shift) + d - 1) / d);
+    }
+    __device__ __forceinline__ unsigned div(unsigned n) const { return (unsigned)(((unsigned long long)n * m) >> shift); }
+};
 
 }  // namespace fa

@@ -1,9 +1,8 @@
 // fa_prefill.hip -- prefill attention forward on gfx950 matrix cores.
 //
 // Work split.  A workgroup owns NS (query head, 32-row block) slots that read
-// the same key/value head: four, or at D = 64 eight on grids large enough to
-// give every CU two or more eight-slot workgroups (1 and 2 exist for the
-// packing ablation).  When the group size G = Hq/Hkv allows, up to four of the slots
+// the same key/value head: four (1, 2 and 8 exist for the packing ablation).
+// When the group size G = Hq/Hkv allows, up to four of the slots
 // are query heads of one key/value group at the same rows -- the GPU form of
 // the inter-head packing of Sec. 4.1.1 and the GQA reuse of Sec. 4.1.2 (iv):
 // every K/V tile staged in LDS serves all slots of the workgroup, and slots
@@ -22,11 +21,26 @@
 //                      lane l^32); scale and log2(e) fold into one
 //                      multiply-add ahead of exp2; weights packed to fp16
 //   O^T += V^T P^T     32x32x16 fp16 MFMA; P straight from the score registers,
-//                      V^T operands read from a transposed copy of the V tile
-//                      that the staging step writes into LDS (a transposing
-//                      LDS read is slower than the plain 16-byte read on
-//                      gfx950, so the transpose is paid once per tile in the
-//                      copy instead of once per wave)
+//                      V^T operands read from the row-major V tile with the
+//                      transposing LDS read
+// Staging.  K tiles, and fp16 V tiles, go from memory to LDS directly (no
+// registers, no LDS store instructions); bf16 V passes through registers to
+// become fp16.  The transposing read (8 bytes a lane) delivers 249 bytes per
+// clock and CU when the four rows that 32 lanes read lie in different quarters
+// of the 64 banks, as much as the plain 16-byte read (255), and 64 to 128
+// when they do not; LDS stores take 62 (4 bytes a lane) to 79 (16 bytes).  So
+// the tiles are laid out for the reads, by swizzling the addresses that a
+// lane loads from, and nothing is transposed in the copy.  Against a copy
+// through registers that wrote V transposed with 4-byte stores, timed in turn:
+// D = 128, 2 x 32/8 heads, 4096 rows, fp16, causal: 299 -> 276 us; D = 64,
+// 16/1 heads, 16384 rows, fp16: 597 -> 581 us; 32/8 heads, 2048 rows, bf16:
+// 30.3 -> 28.9 us.
+// What bounds it.  Large grids run at the card's power limit (1.85 to 2.0 GHz;
+// with zeros for data, at 2.35 GHz, D = 128 takes 184 us and the 16384-row
+// call 447 us), so what saves energy per tile saves time.  At full clock a
+// wave's 32 x 32 block at D = 64 costs about 440 of its SIMD's cycles from
+// registers alone: 256 of MFMA, and 35 vector instructions of 4 cycles and 16
+// exponentials of 8, which overlap with them only in part.
 // The exponent base only moves when a tile's weights against the current base
 // grow too large (see the softmax step below), so the accumulator rescale is
 // skipped on most tiles; sum and accumulator always share the base, so the
@@ -34,7 +48,8 @@
 // A wave's steps run in order; latency is hidden by the other waves of the
 // SIMD (four-slot layouts: two 8-wave workgroups per CU at D = 64, four waves
 // per SIMD within 128 VGPRs; three 4-wave ones at D = 128, three waves per
-// SIMD within 168 VGPRs; their barriers are independent).  Matrix
+// SIMD within 168 VGPRs; their barriers are independent).  With three LDS
+// stages the tile two steps ahead is loaded during a step.  Matrix
 // instructions are issued at raised wave priority.
 // Masked scores are -inf and give exactly 0 (the exponent factor is kept
 // strictly positive, also for scale = 0).  Keys past the end read as zero
@@ -60,9 +75,12 @@ struct PrefillArgs {
     int B, Hq, Hkv, Nq, Nk;
     float c;          // max(|scale|, tiny) * log2(e), > 0
     unsigned qsign;   // 0x80008000 to negate q (scale < 0), else 0
-    int HW;           // query heads per workgroup (1, 2, 4 or 8)
+    int G;            // query heads per key/value head
+    int HW, lgHW;     // query heads per workgroup (1, 2, 4 or 8) and its logarithm
     int nmb;          // row blocks of 32 * (slots / HW) rows
-    int nhg;          // head groups per key/value head (G / HW)
+    Divisor per_mb;   // workgroups per row block: B * Hkv * (G / HW)
+    Divisor nhg;      // head groups per key/value head (G / HW)
+    Divisor nkv;      // key/value heads
     int pair;         // 1: every workgroup is resident at once; order heavy/light pairs
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
     const int *block_table;   // paged K/V: page of each key block (see Problem)
@@ -75,11 +93,11 @@ struct PrefillArgs {
 // SIMD).  D = 128: the accumulator (64 VGPRs) and Q (32) leave no room for
 // that, so one wave per slot (32-key tiles) and 4-wave workgroups, three per
 // CU (three waves per SIMD, from independent workgroups; operands are read
-// from LDS in small groups to fit 168 VGPRs).  Two LDS stages in both.
+// from LDS in small groups to fit 168 VGPRs).  Three LDS stages (two for
+// one- and two-slot workgroups).
 // NS, the slots per workgroup (all reading one key/value head, each staged
-// tile serving all of them), is 4 or, at D = 64 on large grids, 8; 1 and 2
-// exist for the packing ablation (fewer slots stage more per thread, so they
-// hold fewer waves per SIMD).
+// tile serving all of them), is 4; 1, 2 and 8 exist for the packing ablation
+// (fewer slots stage more per thread, so they hold fewer waves per SIMD).
 template <int D, int NS = NSLOT> struct Cfg {
     static constexpr int NQ = D == 64 ? 2 : 1;       // waves per slot
     // waves per SIMD (what the registers allow; fewer slots stage more per thread)
@@ -88,27 +106,20 @@ template <int D, int NS = NSLOT> struct Cfg {
     static constexpr int WPC = NWG >= 4 * WPE ? 1 : 4 * WPE / NWG;   // workgroups per CU (registers)
     static constexpr int BC = 32 * NQ;               // keys per tile
     static constexpr int NT = 64 * NWG;              // threads per workgroup
-    static constexpr int NSTAGE = 2;                 // LDS tile stages
-    static constexpr int KS = D + 8;                 // K row stride in 16-bit elements
-    static constexpr int VTS = BC + 8;               // V^T row stride: BC key positions + pad
-    static constexpr int KSZ = BC * KS;
-    static constexpr int VSZ = D * VTS;
+    static constexpr int NSTAGE = NS >= 4 ? 3 : 2;   // LDS tile stages (small workgroups: two, for room on the CU)
+    static constexpr int AHEAD = NSTAGE - 1;         // a tile is loaded this many steps ahead
+    static constexpr int KSZ = BC * D;               // K tile: BC rows of D elements, chunks swizzled
+    static constexpr int VSZ = BC * D;               // V tile: the same shape
     static constexpr int STAGE = KSZ + VSZ;
     static constexpr int MERGE = NQ > 1 ? NS * (NQ / 2) * ((D / 32) * 16 + 2) * 64 : 0;  // floats
     static constexpr int WORDS = (NSTAGE * STAGE) > (2 * MERGE) ? NSTAGE * STAGE : 2 * MERGE;
-    // Staging split.  KCH 16-byte K chunks and VUN V key-pair units (two
-    // 16-byte loads each) per tile.  With two or more waves the upper half of
-    // the workgroup stages K and the lower half V (SH threads each); a
-    // one-wave workgroup stages both itself.
-    static constexpr int KCH = BC * (D / 8);
-    static constexpr int VUN = (BC / 2) * (D / 8);
-    static constexpr bool BOTH = NT < 128;
-    static constexpr int SH = BOTH ? NT : NT / 2;
-    static constexpr int KPT = KCH / SH;                      // K chunks per staging thread
-    static constexpr int VPT = VUN >= SH ? VUN / SH : 1;      // V units per staging thread
-    static constexpr bool VPART = VUN < SH;                   // only the first VUN V threads stage
-    static constexpr int SL = BOTH ? KPT + 2 * VPT : (KPT > 2 * VPT ? KPT : 2 * VPT);   // loads in flight
-    static_assert(KCH % SH == 0 && (VUN % SH == 0 || SH % VUN == 0), "staging split");
+    // Staging split: a tile is eight 1 KiB pieces of K and eight of V, 64
+    // consecutive 16-byte chunks each.  A wave takes NP pieces of both, or in
+    // a 16-wave workgroup one piece of one (waves 0 .. 7 V, 8 .. 15 K).
+    static constexpr int PIECES = KSZ * 2 / 1024;
+    static constexpr bool SPLIT = NWG > PIECES;
+    static constexpr int NP = SPLIT ? 1 : PIECES / NWG;
+    static_assert(PIECES == 8 && (SPLIT ? NWG == 2 * PIECES : PIECES % NWG == 0), "staging split");
 };
 
 template <typename TIN, typename TOUT, int D, int NS, bool CAUSAL, bool PAGED>
@@ -123,14 +134,13 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     constexpr int CPR = D / 8;              // 16-byte chunks per row
     constexpr bool IN_BF16 = __is_same(TIN, bf16_t);
 
-    __shared__ __attribute__((aligned(16))) unsigned short smem[SM::WORDS];
+    __shared__ __attribute__((aligned(1024))) unsigned short smem[SM::WORDS];
 
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l = tid & 63, lq = l & 31, lh = l >> 5;
     const int kh = w / NSLOT, slot = w % NSLOT;   // kh: the wave's 32 keys of a tile
-    const int RB = NSLOT / a.HW;
-    const int per_mb = a.B * a.Hkv * a.nhg;
+    const int RB = NSLOT >> a.lgHW;
     const int bid = blockIdx.x;
     // Row block of this workgroup.  Latest rows (most keys) first, so that
     // the short causal blocks fill the tail; when the whole grid is resident
@@ -138,15 +148,13 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // long blocks in decreasing and the second half the short ones in
     // increasing length, so that the two workgroups sharing a CU carry about
     // the same total work.
-    const int q_ = bid / per_mb, half_ = (a.nmb + 1) / 2;
+    const int q_ = a.per_mb.div(bid), half_ = (a.nmb + 1) / 2;
     const int mb = (!a.pair || q_ < half_) ? a.nmb - 1 - q_ : q_ - half_;
-    int rest = bid % per_mb;
-    const int hg = rest % a.nhg;
-    rest /= a.nhg;
-    const int g = rest % a.Hkv;
-    const int b = rest / a.Hkv;
-    const int G = a.Hq / a.Hkv;
-    const int hs = slot % a.HW, rs = slot / a.HW;
+    const int rest = bid - q_ * a.per_mb.d;
+    const int bg = a.nhg.div(rest), hg = rest - bg * a.nhg.d;
+    const int b = a.nkv.div(bg), g = bg - b * a.nkv.d;
+    const int G = a.G;
+    const int hs = slot & (a.HW - 1), rs = slot >> a.lgHW;
     const int h = g * G + hg * a.HW + hs;
     const int row0_wg = mb * (WR * RB);
     const int row0 = row0_wg + rs * WR;
@@ -155,7 +163,7 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // Valid keys of this batch element: with per-sequence lengths the K/V
     // tensors hold a.Nk rows per batch element of which the first seqlens[b]
     // are valid, and the queries are the sequence's last Nq positions.
-    const int Nk = a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk;
+    const int Nk = __builtin_amdgcn_readfirstlane(a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk);
     const int off = Nk - Nq;
 
     // Key extents: workgroup, this slot, and keys every row of the slot sees.
@@ -179,59 +187,44 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
         }
     }
 
-    // Tile staging.  The second half of the workgroup copies K rows (chunk
-    // c = st + SH i: key c / CPR, 16-byte column chunk c % CPR); the first
-    // half stages V transposed: unit u holds keys 2p, 2p+1 (p = u % KP) of
-    // column chunk u / KP and writes eight 32-bit words, each the (2p, 2p+1)
-    // pair of one column d, into row d of V^T (as fp16).  Within every 16 keys
-    // the V^T positions swap bits 2 and 3 of the key index, so that the eight
-    // keys one MFMA lane needs are contiguous.  (A one-wave workgroup stages
-    // both: its loads 0 .. KPT-1 are K chunks, the rest V units.)  Loads are
-    // buffer loads: the tile's first key row is the (scalar) base and each
-    // lane keeps a fixed byte offset, so a step spends no vector instructions
-    // on addresses.
-    constexpr int SL = SM::SL;                  // 16-byte loads in flight per thread
-    constexpr int KPT = SM::KPT, VPT = SM::VPT, SH = SM::SH;
-    constexpr bool BOTH = SM::BOTH;
-    constexpr int KP = BC / 2;                  // key pairs per tile
-    static_assert(!(BOTH && PAGED), "paged K/V takes the default slots");
-    // second half of the workgroup: K (wave-uniform).  The older wave of each
-    // SIMD wins issue priority and finishes its softmax first, so it takes the
-    // heavier V staging (the bf16 conversion) and the later one the K copy.
-    const bool kgroup = !BOTH && w >= NT / 128;
-    // the tensor this thread's loads read: K for the K half (and for the
-    // K loads of a one-wave workgroup, whose V loads use vnext below)
-    const S *kvbase = reinterpret_cast<const S *>((kgroup || BOTH) ? a.k : a.v) +
-                      ((size_t)b * a.Nk * a.Hkv + g) * D;
-    const int st = kgroup ? tid - NT / 2 : tid;
-    // loads this thread issues per tile (wave-uniform; FULL: SL for every thread)
-    constexpr bool FULL = !BOTH && KPT == 2 * VPT && !SM::VPART;
-    const int nload = BOTH ? SL : kgroup ? KPT : (SM::VPART && st >= SM::VUN ? 0 : 2 * VPT);
+    // Tile staging.  K, and fp16 V, go from memory to LDS directly (no
+    // registers, no store instructions); bf16 V passes through registers,
+    // where it becomes fp16.  A tile's rows lie in LDS without padding, row r's
+    // 16-byte chunk c at chunk position c ^ kswz(r) (K) or c ^ vswz(r) (V), so
+    // that 16 lanes reading one K chunk of 16 rows, and 32 lanes reading four
+    // V rows' 64-byte segments, meet all 64 banks.  A lane's place in LDS is
+    // fixed by the load (64 consecutive chunks per instruction), so the swizzle
+    // is applied to the address it loads from.  Loads are buffer loads: the
+    // tile's first key row is the (scalar) base and each lane keeps a fixed
+    // byte offset; chunks past the end of the view become zeros.
+    constexpr int NP = SM::NP;
+    const bool dok = !SM::SPLIT || w >= SM::PIECES, dov = !SM::SPLIT || w < SM::PIECES;   // wave-uniform
     const size_t row_elems = (size_t)a.Hkv * D;      // elements between consecutive keys
-    auto isk = [&](int i) __attribute__((always_inline)) { return BOTH ? i < KPT : kgroup; };
-    // tile-relative key and column of load i of this thread
-    auto lkey = [&](int i) __attribute__((always_inline)) {
-        if (isk(i)) return (st + SH * i) / CPR;
-        const int j = BOTH ? i - KPT : i;
-        return 2 * ((st + SH * (j >> 1)) % KP) + (j & 1);
-    };
-    auto lcol = [&](int i) __attribute__((always_inline)) {
-        if (isk(i)) return 8 * ((st + SH * i) % CPR);
-        const int j = BOTH ? i - KPT : i;
-        return 8 * ((st + SH * (j >> 1)) / KP);
-    };
-    int goff[SL];                                    // tile-relative byte offsets
+    const int row_bytes = (int)(row_elems * sizeof(S));
+    auto kswz = [](int r) { return D == 64 ? (r >> 1) & 7 : r & 15; };
+    auto vswz = [](int r) { return D == 64 ? ((r >> 1) & 1) << 2 : (r & 3) << 2; };
+    const int piece = SM::SPLIT ? w % SM::PIECES : w;    // first piece; the next ones NT / 64 further
+    int koff[NP], voff[NP];                              // tile-relative byte offsets
 #pragma unroll
-    for (int i = 0; i < SL; ++i) goff[i] = (int)((lkey(i) * row_elems + lcol(i)) * sizeof(S));
-    uint4_t sr[SL];   // the next tile, in flight during a step
-    // Scalar state of the next tile to load: its first key row, and the bytes
-    // from there to the end of the last key row (the buffer view, so that
-    // keys past the end read as zero); both advance by one tile per load.
-    const S *tnext = kvbase;
-    // a one-wave workgroup: the first key row of the next V tile
-    const S *vnext = reinterpret_cast<const S *>(a.v) + ((size_t)b * a.Nk * a.Hkv + g) * D;
-    long long rem = (long long)(Nk - 1) * (long long)row_elems * (long long)sizeof(S) +
-                    (long long)D * (long long)sizeof(S);
+    for (int j = 0; j < NP; ++j) {
+        const int q = 64 * (piece + (NT / 64) * j) + l, r = q / CPR, c = q % CPR;
+        koff[j] = r * row_bytes + 16 * (c ^ kswz(r));
+        voff[j] = r * row_bytes + 16 * (c ^ vswz(r));
+    }
+    typedef uint4_t vregs_t[IN_BF16 ? NP : 1];
+    vregs_t vr;   // bf16: the next tile's V chunks, in flight during a step
+    // Scalar state of the next tile to load: the address of its first key row
+    // in K and V, which advances by one tile per load, and its number.  The
+    // buffer view of a tile ends after its last valid key (keys past it read
+    // as zero): a full tile's extent for the first Nk / BC tiles, then that of
+    // the remaining keys, if any (one tile's extent fits 31 bits).
+    const size_t head0 = ((size_t)b * a.Nk * a.Hkv + g) * D;
+    const S *ktile = reinterpret_cast<const S *>(a.k) + (PAGED ? 0 : head0);
+    const S *vtile = reinterpret_cast<const S *>(a.v) + (PAGED ? 0 : head0);
+    const int tile_bytes = (BC - 1) * row_bytes + D * (int)sizeof(S);
+    const int full_tiles = Nk / BC;
+    const int last_bytes = Nk % BC ? (Nk % BC - 1) * row_bytes + D * (int)sizeof(S) : 0;
+    int tload = 0;
     // paged K/V: the pool of pages, at head g.  Tiles are loaded in order
     // and a page holds a whole number of tiles, so the page index and the
     // offset inside the page advance without a division.  The table entry of
@@ -239,62 +232,52 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // this sequence's row of the table (entries past the row read as zero),
     // so it has arrived when the page is reached, and no scalar load (whose
     // counter the LDS reads share) is in flight during a step.
-    const S *kvpool = reinterpret_cast<const S *>(kgroup ? a.k : a.v) + (size_t)g * D;
     const __amdgpu_buffer_rsrc_t trs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int *>(PAGED ? a.block_table + (size_t)b * a.max_pages : nullptr), (short)0,
         PAGED ? a.max_pages * 4 : 0, 0x00020000);
     const size_t page_elems = (size_t)a.page_size * row_elems;
-    const int row_bytes = (int)(row_elems * sizeof(S));                 // paged: one key row of the pool
-    const int tile_bytes = (BC - 1) * row_bytes + D * (int)sizeof(S);    // paged: view of a full tile
     int pidx = 0, poff = 0;   // page index and key offset of the next tile
     int tcur = 0, tnx = 0;    // table entries of pages pidx and pidx + 1
     if constexpr (PAGED) {
         tcur = __builtin_amdgcn_raw_buffer_load_b32(trs, 0, 0, 0);
         tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, 4, 0, 0);
     }
-    auto gload = [&](int kt) __attribute__((always_inline)) {   // the next tile (tiles are loaded in order; the argument is its first key)
-        int nrec;
+    const unsigned lds0 = lds_address(smem);
+    // the next tile (they are loaded in order) into stage `stage`; bf16 V into vr
+    auto gload_to = [&](vregs_t &vr, int stage) __attribute__((always_inline)) {
         if constexpr (PAGED) {
             // the tile's rows sit in one page (pages hold a multiple of 64
             // keys, tiles start at multiples of BC): at the start of a page
-            // the base comes from the table (page numbers clamped into the
-            // pool), within it the base advances by one tile per load; the
-            // view ends after the last valid key of the tile (one tile's
-            // extent, which fits 31 bits)
+            // the address comes from the table (page numbers clamped into the
+            // pool), within it the address advances by one tile per load
             if (poff == 0) {
                 const int page = min(max(__builtin_amdgcn_readfirstlane(tcur), 0), a.num_pages - 1);
-                tnext = kvpool + (size_t)page * page_elems;
+                const size_t t = (size_t)g * D + (size_t)page * page_elems;
+                ktile = reinterpret_cast<const S *>(a.k) + t;
+                vtile = reinterpret_cast<const S *>(a.v) + t;
             }
-            const int left = Nk - kt;
-            nrec = left >= BC ? tile_bytes : (left - 1) * row_bytes + D * (int)sizeof(S);
-        } else {
-            // view range, clamped to 31 bits (the tile's own extent always
-            // fits); the halves are opaque so that the test stays two 32-bit
-            // scalar compares instead of one 64-bit vector compare
-            unsigned rlo = (unsigned)rem, rhi = (unsigned)(rem >> 32);
-            asm volatile("" : "+s"(rlo), "+s"(rhi));
-            nrec = (int)(rhi != 0u ? 0x7fffffffu : __builtin_elementwise_min(rlo, 0x7fffffffu));
         }
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(tnext), (short)0, nrec, 0x00020000);
-        if constexpr (BOTH) {
-            const __amdgpu_buffer_rsrc_t rv =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(vnext), (short)0, nrec, 0x00020000);
+        const int nrec = tload < full_tiles ? tile_bytes : last_bytes;
+        ++tload;
+        const unsigned dst = lds0 + stage * (2 * SM::STAGE) + 1024 * piece;
+        if (dok) {
 #pragma unroll
-            for (int i = 0; i < SL; ++i)
-                sr[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(i < KPT ? rs : rv, goff[i], 0, 0));
-            vnext += (size_t)BC * row_elems;
-        } else {
-#pragma unroll
-            for (int i = 0; i < SL; ++i)
-                if (FULL || i < nload)
-                    sr[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, goff[i], 0, 0));
+            for (int j = 0; j < NP; ++j)
+                load_lds16(ktile, nrec, dst + 1024 * (NT / 64) * j, koff[j]);
         }
-        if constexpr (!PAGED) {
-            tnext += (size_t)BC * row_elems;
-            rem -= (long long)BC * (long long)row_elems * (long long)sizeof(S);
-        } else {
-            tnext += (size_t)BC * row_elems;
+        if (dov) {
+            const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(vtile), (short)0, nrec, 0x00020000);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                if constexpr (IN_BF16)
+                    vr[j] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, voff[j], 0, 0));
+                else
+                    load_lds16(vtile, nrec, dst + 2 * SM::KSZ + 1024 * (NT / 64) * j, voff[j]);
+            }
+        }
+        ktile += BC * (size_t)row_elems;
+        vtile += BC * (size_t)row_elems;
+        if constexpr (PAGED) {
             poff += BC;
             const bool cross = poff == a.page_size;   // wave-uniform
             tcur = cross ? tnx : tcur;
@@ -303,43 +286,14 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
             tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, (pidx + 1) * 4, 0, 0);
         }
     };
-    // LDS destination (element offset inside a stage) of load i
-    auto sdst = [&](int i) __attribute__((always_inline)) {
-        if (isk(i)) return lkey(i) * SM::KS + lcol(i);
-        const int key = lkey(i) & ~1;
-        const int pos = (key & ~12) | ((key & 4) << 1) | ((key & 8) >> 1);
-        return SM::KSZ + lcol(i) * SM::VTS + pos;   // row d = lcol + e, position pos
-    };
-    auto sstore_v = [&](unsigned short *stage, int i0) __attribute__((always_inline)) {   // the V unit of loads i0, i0 + 1
-        unsigned *vt = reinterpret_cast<unsigned *>(stage + sdst(i0));
-        const uint4_t x = sr[i0], y = sr[i0 + 1];
+    // bf16 V of a loaded tile, as fp16, into its stage
+    auto vstore_from = [&](const vregs_t &vr, unsigned short *stage) __attribute__((always_inline)) {
+        if constexpr (IN_BF16) {
+            if (dov) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const unsigned xe = x[e >> 1], ye = y[e >> 1];
-            unsigned w;
-            if constexpr (IN_BF16) {
-                const float fx = __uint_as_float((e & 1) ? (xe & 0xffff0000u) : (xe << 16));
-                const float fy = __uint_as_float((e & 1) ? (ye & 0xffff0000u) : (ye << 16));
-                w = pack_f16x2(fx, fy);
-            } else {
-                w = (e & 1) ? __builtin_amdgcn_perm(ye, xe, 0x07060302u)
-                            : __builtin_amdgcn_perm(ye, xe, 0x05040100u);
+                for (int j = 0; j < NP; ++j)
+                    st16(stage + SM::KSZ + 512 * (piece + (NT / 64) * j) + 8 * l, bf16x8_to_f16x8(vr[j]));
             }
-            vt[e * (SM::VTS / 2)] = w;
-        }
-    };
-    auto sstore = [&](unsigned short *stage) __attribute__((always_inline)) {
-        if constexpr (BOTH) {
-#pragma unroll
-            for (int i = 0; i < KPT; ++i) st16(stage + sdst(i), sr[i]);
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) sstore_v(stage, KPT + 2 * u);
-        } else if (kgroup) {
-#pragma unroll
-            for (int i = 0; i < KPT; ++i) st16(stage + sdst(i), sr[i]);
-        } else if (FULL || nload > 0) {
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) sstore_v(stage, 2 * u);
         }
     };
 
@@ -349,17 +303,31 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     float m_run = -INFINITY;   // exponent base (log2 domain), same in lanes l and l^32
     float l_run = 0.f;         // this lane's part of the row sum
     float nbase = 0.f;         // -m_run, or 0 while the row has no base
-    bool fresh = true;         // some row of the wave has no base yet (wave-uniform)
+    float lim = -INFINITY;     // largest lane sum kept without a rescale; below any sum while the row has no base
 
-    const int k_lane = (32 * kh + lq) * SM::KS + 8 * lh;
-    const int v_lane = SM::KSZ + lq * SM::VTS + 32 * kh + 8 * lh;
+    // LDS offsets (elements) of the lane's operands.  K: chunk 2 kk + lh of row
+    // 32 kh + lq.  V: the transposing read gives a lane four keys of one column;
+    // lane i of each 16 addresses row i / 4 of four, columns 4 (i % 4) .. + 3 of
+    // 16, and the group of 16 picks the column half; k-step j takes keys 16 j +
+    // 4 lh .. + 3 and 16 j + 8 + 4 lh .. + 3, the order of the weights.
+    const int k_row = (32 * kh + lq) * D, k_sw = 8 * (lh ^ kswz(lq));
+    auto kat = [&](const unsigned short *stage, int kk) {
+        return as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_row + ((16 * kk) ^ k_sw)));
+    };
+    const int v_j = l & 15;
+    const int v_row = SM::KSZ + (32 * kh + 4 * lh + (v_j >> 2)) * D + 16 * ((l >> 4) & 1) + 4 * (v_j & 3);
+    const int v_sw = 8 * vswz(v_j >> 2);
+    auto vat = [&](const unsigned short *stage, int dt, int j) {
+        const _Float16 *p = reinterpret_cast<const _Float16 *>(stage) + v_row + ((32 * dt) ^ v_sw) + 16 * D * j;
+        return cat_half8(lds_read_tr16(p), lds_read_tr16(p + 8 * D));
+    };
     auto stage_at = [&](int r) { return smem + r * SM::STAGE; };
 
     // K operands of this wave's 32 keys of the tile held in `stage`
     auto kread = [&](const unsigned short *stage, V8 (&ka)[KSTEPS]) {
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk)
-            ka[kk] = as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_lane + 16 * kk));
+            ka[kk] = kat(stage, kk);
     };
     // S^T = K Q^T.  Matrix instructions are issued at raised wave priority:
     // the SIMD then starts a wave's next MFMA as soon as the matrix core is
@@ -382,8 +350,7 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     auto vread = [&](const unsigned short *stage, half8_t (&va)[KSTEPS]) {
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk)
-            va[kk] = as_vec8<half8_t>(*reinterpret_cast<const uint4_t *>(
-                stage + v_lane + 32 * (kk >> 1) * SM::VTS + 16 * (kk & 1)));
+            va[kk] = vat(stage, kk >> 1, kk & 1);
     };
     // O^T += V^T P^T with the weights of one tile (k-step j = keys 16 j .. 16 j
     // + 15 of the wave's half)
@@ -404,14 +371,14 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     auto scores_jit = [&](const unsigned short *stage) {
         float16_t s = float16_t{};
         V8 cur0, cur1, nxt0, nxt1;
-        cur0 = as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_lane));
-        cur1 = as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_lane + 16));
+        cur0 = kat(stage, 0);
+        cur1 = kat(stage, 1);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int g = 0; g < KSTEPS / 2; ++g) {
             if (g + 1 < KSTEPS / 2) {
-                nxt0 = as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_lane + 32 * (g + 1)));
-                nxt1 = as_vec8<V8>(*reinterpret_cast<const uint4_t *>(stage + k_lane + 32 * (g + 1) + 16));
+                nxt0 = kat(stage, 2 * (g + 1));
+                nxt1 = kat(stage, 2 * (g + 1) + 1);
             }
             s = mfma32(cur0, qf[2 * g], s);
             s = mfma32(cur1, qf[2 * g + 1], s);
@@ -424,14 +391,14 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     };
     auto pv_jit = [&](const half8_t &p0, const half8_t &p1, const unsigned short *stage) {
         half8_t cur0, cur1, nxt0, nxt1;
-        cur0 = as_vec8<half8_t>(*reinterpret_cast<const uint4_t *>(stage + v_lane));
-        cur1 = as_vec8<half8_t>(*reinterpret_cast<const uint4_t *>(stage + v_lane + 16));
+        cur0 = vat(stage, 0, 0);
+        cur1 = vat(stage, 0, 1);
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
             if (dt + 1 < DT) {
-                nxt0 = as_vec8<half8_t>(*reinterpret_cast<const uint4_t *>(stage + v_lane + 32 * (dt + 1) * SM::VTS));
-                nxt1 = as_vec8<half8_t>(*reinterpret_cast<const uint4_t *>(stage + v_lane + 32 * (dt + 1) * SM::VTS + 16));
+                nxt0 = vat(stage, dt + 1, 0);
+                nxt1 = vat(stage, dt + 1, 1);
             }
             oacc[dt] = mfma32(cur0, p0, oacc[dt]);
             oacc[dt] = mfma32(cur1, p1, oacc[dt]);
@@ -487,8 +454,8 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
         exp_pack(s, nbase, p0, p1);
         const float l_old = l_run;
         l_run = add_sum(l_run, p0, p1);
-        const bool over = !(l_run <= l_old + kMaxLaneSum);
-        if (fresh || __builtin_amdgcn_ballot_w64(over) != 0) {
+        const bool over = !(l_run <= l_old + lim);
+        if (__builtin_amdgcn_ballot_w64(over) != 0) {
             float mx = max3(s[0], s[1], s[2]);
             mx = max3(mx, s[3], s[4]);
             mx = max3(mx, s[5], s[6]);
@@ -506,7 +473,7 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
             for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
             exp_pack(s, nbase, p0, p1);
             l_run = add_sum(l_old * alpha, p0, p1);
-            fresh = __builtin_amdgcn_ballot_w64(m_run == -INFINITY) != 0;
+            lim = (m_new == -INFINITY) ? -INFINITY : kMaxLaneSum;
         }
     };
 
@@ -515,19 +482,33 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // to the other LDS stage at the end of the step.  The latencies of a
     // step are hidden by the waves of the other workgroups on the CU, whose
     // barriers are independent of this one's.
+    // Tile i + AHEAD is loaded during step i.  Two steps ahead, its bf16 V goes
+    // to its stage in step i + 1, before the next loads; one step ahead, at the
+    // end of step i.
+    constexpr int AHEAD = SM::AHEAD;
     if (ntiles > 0) {
-        gload(0);
-        sstore(stage_at(0));
+        vregs_t v0;
+        gload_to(v0, 0);
+        if (AHEAD == 2 && ntiles > 1) gload_to(vr, 1);
+        vstore_from(v0, stage_at(0));
+        if (AHEAD == 2 && ntiles > 1)
+            lds_loads_done<SM::SPLIT ? NP : 2 * NP>();   // all but those of tile 1
+        else
+            lds_loads_done<0>();
     }
-    __syncthreads();
-    auto step = [&](int i, auto R) {   // R: stage of tile i (i % 2)
+    lds_barrier();
+    auto step = [&](int i, auto R) {   // R: stage of tile i (i % NSTAGE)
         constexpr int r = decltype(R)::value;
-        const bool more = i + 1 < ntiles;
         // the next tile's loads are issued after the K operand reads (their
         // scalar set-up then overlaps the LDS latency, and at D = 128 their
         // registers are not live across the QK^T product)
         float16_t s = D == 128 ? scores_jit(stage_at(r)) : scores(stage_at(r));
-        if (more) gload((i + 1) * BC);
+        if (AHEAD == 2 && i + 1 < ntiles) {
+            lds_loads_done<0>();   // tile i + 1, loaded since the previous step
+            vstore_from(vr, stage_at((r + 1) % NSTAGE));
+        }
+        const bool more = i + AHEAD < ntiles;
+        if (more) gload_to(vr, (r + AHEAD) % NSTAGE);
         mask(s, i);
         half8_t p0, p1;
         half8_t va[KSTEPS];
@@ -540,15 +521,19 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
         } else {
             pv(p0, p1, va);
         }
-        if (more) sstore(stage_at(r ^ 1));
-        __syncthreads();
+        if (AHEAD == 1) {
+            if (more) vstore_from(vr, stage_at((r + AHEAD) % NSTAGE));
+            lds_loads_done<0>();
+        }
+        lds_barrier();
     };
-    int i = 0;
-    for (; i + 2 <= ntiles; i += 2) {   // unrolled by two: stage offsets are constants
+    for (int i = 0; i < ntiles; i += NSTAGE) {   // unrolled over the stages: their offsets are constants
         step(i, std::integral_constant<int, 0>{});
-        step(i + 1, std::integral_constant<int, 1>{});
+        if (i + 1 < ntiles) step(i + 1, std::integral_constant<int, 1>{});
+        if constexpr (NSTAGE > 2) {
+            if (i + 2 < ntiles) step(i + 2, std::integral_constant<int, 2>{});
+        }
     }
-    if (i < ntiles) step(i, std::integral_constant<int, 0>{});
     __syncthreads();   // the merge below reuses the stage memory
 
     // ---- merge the two key halves of each slot through LDS
@@ -643,11 +628,15 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.HW = p.hw > 0 ? p.hw : hw;
     const int RB = NS / a.HW;
     a.nmb = (p.Nq + WR * RB - 1) / (WR * RB);
-    a.nhg = G / a.HW;
     a.pair = 0;
-    const long long nblocks = (long long)a.nmb * p.B * p.Hkv * a.nhg;
+    const long long nblocks = (long long)a.nmb * p.B * p.Hkv * (G / a.HW);
     if (nblocks <= 0) return hipSuccess;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    a.G = G;
+    a.lgHW = a.HW == 8 ? 3 : a.HW == 4 ? 2 : a.HW == 2 ? 1 : 0;
+    a.nhg = Divisor(G / a.HW);
+    a.nkv = Divisor(p.Hkv);
+    a.per_mb = Divisor((unsigned)p.B * p.Hkv * (G / a.HW));   // <= nblocks
     if (p.causal) a.pair = nblocks <= (long long)SM::WPC * cu_count() ? 1 : 0;
     if constexpr (NS == NSLOT) {
         if (p.block_table) {
@@ -663,28 +652,15 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Default slots per workgroup: 8 at D = 64 when the grid of 8-slot
-// workgroups (the default heads, up to 4, times 2 row blocks) still gives
-// every CU at least two of them -- each staged tile then serves twice the
-// rows (MQA prefill, 16 heads on one K/V head, 16384 rows: 578 against
-// 602 us); 4 otherwise: on a small grid (the 32-head, 2048-row GQA prefill:
-// 39 against 31.5 us), at D = 128 (the eight-slot workgroup holds two waves
-// per SIMD instead of three; on the 32-head, 4096-row prefill it ran from
-// 2 % faster to 3 % slower depending on the box), for paged K/V and when the
-// caller fixed the heads per workgroup.
-int default_slots(const Problem &p) {
-    if (p.D != 64 || p.block_table || p.hw > 0) return NSLOT;
-    const int G = p.Hq / p.Hkv;
-    const int hw = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-    const int rows = WR * (8 / hw);
-    const long long nblocks = (long long)((p.Nq + rows - 1) / rows) * p.B * p.Hkv * (G / hw);
-    const int cus = cu_count();
-    return cus > 0 && nblocks >= 2LL * cus ? 8 : NSLOT;
-}
-
+// Slots per workgroup: four unless the caller asks for another layout.  With
+// the tiles staged without registers or LDS stores, eight slots per staged
+// tile save too little to make up for the coarser workgroups (D = 64, timed in
+// one process, four against eight: 32/4 heads, 5001 rows, fp16 131 against 142
+// us; 32/8 heads, 8192 rows, bf16 325 against 329; 16/1 heads, 16384 rows,
+// fp16 613 against 612, bf16 624 against 621).
 template <typename TIN, typename TOUT, int D, bool CAUSAL>
 hipError_t launch_s(const Problem &p, hipStream_t s) {
-    switch (p.slots > 0 ? p.slots : default_slots(p)) {
+    switch (p.slots) {
     case 1: return launch_t<TIN, TOUT, D, 1, CAUSAL>(p, s);
     case 2: return launch_t<TIN, TOUT, D, 2, CAUSAL>(p, s);
     case 8: return launch_t<TIN, TOUT, D, 8, CAUSAL>(p, s);
