@@ -19,7 +19,17 @@
 // arithmetic.  The waves' partial states are merged through LDS and the
 // workgroup writes one (unnormalised accumulator, max, sum) triple per query
 // head and split.  A second kernel merges the splits of each (batch, query
-// head) by their log-sum-exp and applies the final 1/l normalisation.
+// head) by their log-sum-exp and applies the final 1/l normalisation; with one
+// split the workgroup writes the result itself.  A sequence's own valid keys
+// are spread evenly over the splits, so that short sequences of a batch occupy
+// their workgroups no longer than they must.
+//
+// What bounds it: HBM for large caches (16 x 32/8 heads, 8192 keys, D = 128:
+// 82 us for 537 MB, 6.5 TB/s against 6.9 for a plain read), and how evenly the
+// last round of workgroups fills the chip (see decode_default_splits); for
+// small ones the chain launch, lengths, keys, merge, second launch (7 us for
+// 32/4 heads, 1537 keys, D = 64).  Loads two chunks ahead (144 and 244
+// registers) and 16-wave workgroups at D = 64 gained nothing.
 #include "fa_common.h"
 #include "fa_internal.h"
 
@@ -27,24 +37,31 @@ namespace fa {
 namespace {
 
 constexpr int KPW = 32;        // keys per wave iteration
-constexpr int NW = 8;          // waves per workgroup
 constexpr int QG = 16;         // query heads per MFMA column block
+constexpr int NW = 8;          // waves per workgroup
 constexpr float TAU = 8.0f;    // lazy-rescale threshold (log2 units)
 constexpr int MIN_KEYS_PER_SPLIT = 256;
-constexpr int TARGET_WORKGROUPS = 256;   // about one workgroup per CU: long splits, few partials
+constexpr int CUS = 256;                 // compute units
+constexpr long long LONG_SPLIT = 4096 * 100;   // keys (hundredths) beyond which one workgroup fills a CU's share of HBM
+constexpr int MAX_ROUNDS = 8;            // most rounds of one workgroup per CU that splitting may make
 
 struct DecodeArgs {
     const void *q, *k, *v;
     float *opart, *mpart, *lpart;   // workspace: [B*Hq*S*D], [B*Hq*S], [B*Hq*S]
-    int B, Hq, Hkv, Nk;
-    int S;          // splits
-    int chunk;      // keys per split (multiple of KPW)
-    int nqg;        // 16-head query groups per key/value head
+    void *o;        // written directly when there is one split
+    float *lse;
+    int out_f32;    // o holds fp32 instead of the input type
+    int Hq, Hkv, Nk;
+    int G;          // query heads per key/value head
+    Divisor S;      // splits
+    Divisor nqg;    // 16-head query groups per key/value head
+    Divisor nkv;    // key/value heads
     float c;        // |scale| * log2(e)
     unsigned qsign; // sign flip of q for negative scale
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
     const int *block_table;   // paged K/V: page of each key block (see Problem)
-    int page_size, max_pages, num_pages;
+    Divisor page_size;
+    int max_pages, num_pages;
 };
 
 template <int D> struct DSmem {
@@ -75,20 +92,21 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
 
     __shared__ __attribute__((aligned(16))) unsigned char smem[SM::BYTES];
 
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    const int tid = threadIdx.x, l = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lc = l & 15, lg = l >> 4;            // MFMA column (query) and k-group
-    int bid = blockIdx.x;
-    const int s = bid % a.S;
-    bid /= a.S;
-    const int qg = bid % a.nqg;
-    bid /= a.nqg;
-    const int g = bid % a.Hkv;
-    const int b = bid / a.Hkv;
-    const int G = a.Hq / a.Hkv;
-    // valid keys of this batch element (a cache of a.Nk rows per element)
-    const int Nk = a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk;
-    const int k0 = s * a.chunk;
-    const int k1 = min(Nk, k0 + a.chunk);
+    const int bid = blockIdx.x;
+    const int u = a.S.div(bid), s = bid - u * a.S.d;
+    const int u2 = a.nqg.div(u), qg = u - u2 * a.nqg.d;
+    const int b = a.nkv.div(u2), g = u2 - b * a.nkv.d;
+    const int G = a.G;
+    // valid keys of this batch element (a cache of a.Nk rows per element), and
+    // its split: the sequence's own keys, spread evenly in multiples of KPW
+    const int Nk = __builtin_amdgcn_readfirstlane(a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk);
+    const unsigned whole = a.S.div(Nk), per = whole + (whole * a.S.d != (unsigned)Nk);   // ceil(Nk / S)
+    const long long chunk = (per + (KPW - 1)) & ~(unsigned)(KPW - 1);
+    const int k0 = (int)min(s * chunk, (long long)Nk);
+    const int k1 = (int)min(k0 + chunk, (long long)Nk);
 
     // This lane's query head (MFMA column) and its Q operand.
     const int qh = qg * QG + lc;             // index inside the group
@@ -106,9 +124,8 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
         }
     }
 
-    const S *kbase = reinterpret_cast<const S *>(a.k);
-    const S *vbase = reinterpret_cast<const S *>(a.v);
-    const size_t row_stride = (size_t)a.Hkv * D;                  // elements between keys
+    const size_t row_elems = (size_t)a.Hkv * D;                   // elements between keys
+    const int row_bytes = (int)(row_elems * sizeof(S));
     const size_t head_off = ((size_t)b * a.Nk * a.Hkv + g) * D;   // key 0 of (b, g)
 
     unsigned short *kst = reinterpret_cast<unsigned short *>(smem) + w * SM::WAVE;
@@ -125,31 +142,42 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
     // A chunk's K and V rows are loaded whole (64 lanes cover 64 / CPR
     // complete rows per instruction, the access pattern that streams from HBM
     // fastest) and staged in the wave's own LDS area: K as is (read back in
-    // the MFMA operand layout), V as fp16 (read back transposed).
+    // the MFMA operand layout), V as fp16 (read back transposed).  Loads go
+    // through a buffer view that ends after the chunk's last key, so that keys
+    // past it read as zeros without a branch, and each wait covers exactly the
+    // chunk it needs.
+    int off[RLOADS];
+#pragma unroll
+    for (int i = 0; i < RLOADS; ++i) off[i] = (l + 64 * i) / CPR * row_bytes + 16 * ((l + 64 * i) % CPR);
+    const int nchunks = (k1 - k0 + KPW - 1) / KPW;
     uint4_t kr[RLOADS], vr[RLOADS];   // the next chunk's rows, in flight
-    auto gload = [&](int kb) {
-        // element offset of key kb's row (head g): contiguous, or through the
-        // block table (a chunk never crosses a page: chunks start at multiples
-        // of 32 keys and pages hold a multiple of 64; page numbers are clamped
-        // into the pool)
-        size_t rbase;
+    auto gload = [&](int ch) __attribute__((always_inline)) {
+        // first key of the chunk (past the last chunk: an empty view)
+        const int kb = k0 + ch * KPW;
+        const int n = ch < nchunks ? min(k1 - kb, KPW) : 0;
+        const int nrec = n > 0 ? (n - 1) * row_bytes + D * (int)sizeof(S) : 0;
+        // its row, contiguous or through the block table (a chunk never
+        // crosses a page: chunks start at multiples of 32 keys and pages hold
+        // a multiple of 64; page numbers are clamped into the pool)
+        size_t rbase = 0;
         if constexpr (PAGED) {
-            const int pi = kb / a.page_size;
-            const int page = min(max(a.block_table[(size_t)b * a.max_pages + pi], 0), a.num_pages - 1);
-            rbase = ((size_t)page * a.page_size + (kb - pi * a.page_size)) * row_stride + (size_t)g * D;
+            if (n > 0) {
+                const int pi = a.page_size.div(kb);
+                const int page = min(max(a.block_table[(size_t)b * a.max_pages + pi], 0), a.num_pages - 1);
+                rbase = ((size_t)page * a.page_size.d + (kb - pi * (int)a.page_size.d)) * row_elems + (size_t)g * D;
+            }
         } else {
-            rbase = head_off + (size_t)kb * row_stride;
+            rbase = head_off + (size_t)(n > 0 ? kb : 0) * row_elems;
         }
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<S *>(reinterpret_cast<const S *>(a.k)) + rbase, (short)0, nrec, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<S *>(reinterpret_cast<const S *>(a.v)) + rbase, (short)0, nrec, 0x00020000);
+        constexpr int NT = 2;   // read once: non-temporal
 #pragma unroll
         for (int i = 0; i < RLOADS; ++i) {
-            const int c = l + 64 * i;
-            const int kc = c / CPR, cc = c % CPR;
-            kr[i] = uint4_t{0u, 0u, 0u, 0u};
-            vr[i] = uint4_t{0u, 0u, 0u, 0u};
-            if (kb + kc < k1) {
-                kr[i] = ld16_stream(kbase + rbase + kc * row_stride + 8 * cc);
-                vr[i] = ld16_stream(vbase + rbase + kc * row_stride + 8 * cc);
-            }
+            kr[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(rk, off[i], 0, NT));
+            vr[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(rv, off[i], 0, NT));
         }
     };
     auto kvstore = [&]() {
@@ -162,16 +190,12 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
         }
     };
 
-    const int nchunks = (k1 > k0) ? (k1 - k0 + KPW - 1) / KPW : 0;
-    if (w < nchunks) {
-        gload(k0 + w * KPW);
-        kvstore();
-        wave_lds_fence();
-    }
+    gload(w);
     for (int ch = w; ch < nchunks; ch += NW) {
         const int kb = k0 + ch * KPW;
-        const bool more = ch + NW < nchunks;
-        if (more) gload(kb + NW * KPW);
+        kvstore();
+        gload(ch + NW);
+        wave_lds_fence();
         // ---- S^T = K Q^T: two 16-key halves, lane owns query lc, keys 4 lg + r
         float4_t s0 = float4_t{}, s1 = float4_t{};
         const unsigned short *kl = kst + lc * SM::KS + 8 * lg;
@@ -226,11 +250,7 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
             half8_t va = cat_half8(lds_read_tr16(vp), lds_read_tr16(vp + 16 * SM::VS));
             oacc[dt] = mfma16(va, pf, oacc[dt]);
         }
-        if (more) {
-            wave_lds_fence();   // operand reads of this chunk are done
-            kvstore();
-            wave_lds_fence();
-        }
+        wave_lds_fence();   // operand reads of this chunk are done
     }
 
     // ---- merge the waves' partial states through LDS
@@ -263,19 +283,35 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
             wgt[ww] = (mw == -INFINITY) ? 0.f : exp2_fast(mw - M);
             L += wgt[ww] * mf[(ww * QG + mq) * (D + 2) + D + 1];
         }
-        const size_t slot = ((size_t)b * a.Hq + g * G + mh) * a.S + s;
-        float *op = a.opart + slot * D;
+        const size_t bh = (size_t)b * a.Hq + g * G + mh;
+        const bool direct = a.S.d == 1;   // one split: the result itself
+        const size_t slot = bh * a.S.d + s;   // (bh itself with one split)
+        // a sequence with no valid key (per-sequence lengths) gives 0 and -inf
+        const float inv = direct ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
+        float acc[D / 16];
 #pragma unroll
         for (int j = 0; j < D / 16; ++j) {
-            const int d = part + 16 * j;
-            float acc = 0.f;
+            acc[j] = 0.f;
 #pragma unroll
-            for (int ww = 0; ww < NW; ++ww) acc += wgt[ww] * mf[(ww * QG + mq) * (D + 2) + d];
-            op[d] = acc;
+            for (int ww = 0; ww < NW; ++ww) acc[j] += wgt[ww] * mf[(ww * QG + mq) * (D + 2) + part + 16 * j];
+            acc[j] *= inv;
+        }
+        if (!direct || a.out_f32) {
+            float *op = (direct ? reinterpret_cast<float *>(a.o) : a.opart) + slot * D + part;
+#pragma unroll
+            for (int j = 0; j < D / 16; ++j) op[16 * j] = acc[j];
+        } else {
+            S *op = reinterpret_cast<S *>(a.o) + slot * D + part;
+#pragma unroll
+            for (int j = 0; j < D / 16; ++j) op[16 * j] = from_f32<S>(acc[j]);
         }
         if (part == 0) {
-            a.mpart[slot] = M;
-            a.lpart[slot] = L;
+            if (!direct) {
+                a.mpart[slot] = M;
+                a.lpart[slot] = L;
+            } else if (a.lse) {
+                a.lse[bh] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+            }
         }
     }
 }
@@ -337,20 +373,23 @@ hipError_t launch_t(const Problem &p, int S, void *ws, hipStream_t stream) {
     a.opart = reinterpret_cast<float *>(ws);
     a.mpart = a.opart + nslot * D;
     a.lpart = a.mpart + nslot;
-    a.B = p.B; a.Hq = p.Hq; a.Hkv = p.Hkv; a.Nk = p.Nk;
-    a.S = S;
-    const int per = (p.Nk + S - 1) / S;
-    a.chunk = (per + KPW - 1) / KPW * KPW;
-    const int G = p.Hq / p.Hkv;
-    a.nqg = (G + QG - 1) / QG;
+    a.o = p.o;
+    a.lse = p.lse;
+    a.out_f32 = p.out == FA_F32;
+    a.Hq = p.Hq; a.Hkv = p.Hkv; a.Nk = p.Nk;
+    const int G = p.Hq / p.Hkv, nqg = (G + QG - 1) / QG;
+    a.G = G;
+    a.S = Divisor(S);
+    a.nqg = Divisor(nqg);
+    a.nkv = Divisor(p.Hkv);
     a.c = __builtin_fabsf(p.scale) * kLog2e;
     a.qsign = p.scale < 0.f ? 0x80008000u : 0u;
     a.seqlens = p.seqlens;
     a.block_table = p.block_table;
-    a.page_size = p.page_size;
+    a.page_size = Divisor(p.block_table ? p.page_size : 1);
     a.max_pages = p.max_pages;
     a.num_pages = p.num_pages;
-    const long long nblocks = (long long)p.B * p.Hkv * a.nqg * S;
+    const long long nblocks = (long long)p.B * p.Hkv * nqg * S;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     if (p.block_table)
         hipLaunchKernelGGL((decode_split_kernel<TIN, D, true>), dim3((unsigned)nblocks), dim3(64 * NW), 0,
@@ -359,7 +398,7 @@ hipError_t launch_t(const Problem &p, int S, void *ws, hipStream_t stream) {
         hipLaunchKernelGGL((decode_split_kernel<TIN, D, false>), dim3((unsigned)nblocks), dim3(64 * NW), 0,
                            stream, a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || S == 1) return e;
     hipLaunchKernelGGL((decode_combine_kernel<TOUT, D>), dim3((unsigned)(p.B * p.Hq)), dim3(D), 0,
                        stream, a.opart, a.mpart, a.lpart, p.o, p.lse, S);
     return hipGetLastError();
@@ -376,16 +415,43 @@ bool decode_supported(int Nq, int D, fa_dtype_t in) {
     return Nq == 1 && (D == 64 || D == 128) && (in == FA_F16 || in == FA_BF16);
 }
 
+// Split count.  A call has U (batch, key/value head, query group) units and
+// runs U S workgroups, as many at once as the chip holds: one per CU at
+// D = 128 (143 KB of LDS), two at D = 64.  What counts is that the last round
+// is full: 12 units of 2 heads at 6144 keys, D = 128, take 23.6 us with 11
+// splits (264 workgroups on 256 CUs) and 18.8 with 10; 9 x 8 at 8839 keys,
+// D = 64: 47.2 with 4 (288), 31.5 with 7 (504).  So the candidates are the
+// largest counts that fill j rounds of 256, j = 1 .. 8, and one split, and the
+// cheapest is taken by a model in keys: a round costs its keys per split (half
+// where it leaves a CU one workgroup instead of two: 52 % below 4096 keys, 50
+// above, where one streams as fast as two) plus some 250 for the workgroup's
+// start and end; more than one split adds the merge kernel (some
+// 200) and its loads (4 a split).  The model picks a count within 6 % of the
+// best of those measured (a dozen shapes from 24 to 720 units, 512 to 32768
+// keys).  At least 256 keys per split (one chunk for each wave).
 int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D) {
-    (void)D;
     const int G = Hq / Hkv;
     const long long units = (long long)B * Hkv * ((G + QG - 1) / QG);
-    long long s = (TARGET_WORKGROUPS + units - 1) / units;
-    const long long cap = (Nk + MIN_KEYS_PER_SPLIT - 1) / MIN_KEYS_PER_SPLIT;
-    if (s > cap) s = cap;
-    if (s < 1) s = 1;
-    if (s > FA_MAX_SPLITS) s = FA_MAX_SPLITS;
-    return (int)s;
+    long long cap = (Nk + (long long)MIN_KEYS_PER_SPLIT - 1) / MIN_KEYS_PER_SPLIT;
+    if (cap > FA_MAX_SPLITS) cap = FA_MAX_SPLITS;
+    const long long slots = D == 64 ? 2 * CUS : CUS;   // workgroups the chip holds
+    long long best = 1, least = 0;
+    for (int j = 0; j <= MAX_ROUNDS; ++j) {
+        long long S = j == 0 ? 1 : j * (long long)CUS / units;
+        if (S > cap) S = cap;
+        if (S < 1 || (j > 0 && S == 1)) continue;
+        const long long W = units * S, full = W / slots, rest = W % slots;
+        const long long keys = 100 * (long long)Nk / S;   // hundredths of a key, as the costs
+        long long cost = full * (keys + 25000);
+        if (rest > 0) cost += (slots > CUS && rest <= CUS ? keys * (keys > LONG_SPLIT ? 50 : 52) / 100 : keys) + 25000;
+        if (S > 1) cost += 20000 + 400 * S;
+        if (j == 0 || cost < least) {
+            least = cost;
+            best = S;
+        }
+        if (j > 0 && S == cap) break;
+    }
+    return (int)best;
 }
 
 size_t decode_workspace_bytes(int B, int Hq, int D, int splits) {
