@@ -3,36 +3,53 @@
 // a head dimension other than 64 or 128 (any D with D % 8 == 0 and D <= 256),
 // prefill and decode.
 //
-// Everything after the loads is fp32: scores are fp32 sums, the weights stay
-// fp32 and multiply fp32 values.  Both products run on the matrix cores:
-//   S^T = K Q^T   fp32 inputs: 16x16x4 fp32 MFMA; fp16 / bf16: 16x16x32 MFMA
-//                 of the inputs as they are (exact products, fp32 sums)
-//   O^T += V^T P^T   16x16x4 fp32 MFMA; P straight from the score registers
-//                 (step r takes key 4 (l / 16) + r of every lane group), V from
-//                 LDS in fp32 (fp16 / bf16 values are widened while staged)
+// Scores are fp32 sums; weights, their sums and the accumulators are fp32.
+// Both products run on the matrix cores:
+//   S^T = K Q^T   fp32 inputs: 16x16x4 fp32 MFMA (the rows of K taken in the
+//                 order 4 (i % 4) + i / 4); fp16 / bf16: 16x16x32 MFMA of the
+//                 inputs as they are (exact products, fp32 sums)
+//   O^T += V^T P^T, P straight from the score registers.  fp32 inputs: 16x16x4
+//                 fp32 MFMA.  fp16 / bf16: the inputs' 16x16x32 MFMA with each
+//                 fp32 weight as the sum of three 16-bit terms, which holds all
+//                 its 24 bits; products are exact, sums fp32.  Three of those
+//                 take 48 cycles for 32 keys, eight fp32 ones 256.  V^T operands
+//                 by the transposing LDS read.
 //
 // Work split.  The Nq * G query rows of the G heads that read one key/value
 // head are numbered together, v = row * G + head, and 16 consecutive ones are
 // the columns of a wave's matrix products, so a group's heads share every
 // staged key and a decode call (Nq = 1) fills columns with heads.  A workgroup
-// of eight waves is NSLOT slots of 16 columns times KSP key parts: a tile of
-// 16 KSP keys is staged in LDS for all of them (the next tile's loads are in
-// flight meanwhile) and part j takes its keys 16 j .. 16 j + 15.  The parts'
-// states are merged through LDS at the end.
+// is NSLOT slots of 16 columns times KSP key parts: a tile of KSP * 16 NB keys
+// is staged in LDS for all of them, memory to LDS directly (two stages, the
+// next tile's loads are in flight during a step), and part j takes its keys
+// 16 NB j ...  The parts' states are merged through LDS at the end.
 //
-// What bounds it: the fp32 MFMA (64 flop per cycle and SIMD).  One wave's
-// 16 x 16 block takes D / 4 score and D / 4 value steps of 32 cycles, against
-// D / 4 16-byte and D / 4 4-byte LDS reads, a quarter of what LDS delivers.
+// What bounds it.  fp32: the fp32 MFMA (64 flop per cycle and SIMD; a wave's
+// 16 x 16 block takes D / 4 score and D / 4 value steps of 32 cycles) with the
+// softmax's vector instructions on top, about 25 to 40 for four scores a lane;
+// with four waves a SIMD, 2900 cycles a step at D = 64 of which 2048 are MFMA.
+// 16 bits: instruction issue, about 150 vector instructions and 4 DP / 16 MFMA
+// of 16 cycles a wave's step of 32 keys, and the staging, some 50 bytes per
+// clock and CU; a step of one workgroup alone on its CU takes 1800 cycles at
+// D = 96 (the loads' issue 600, scores 350, softmax 500, values 490).  The base
+// of the weights moves rarely (see GROWTH): a rescale in nearly every step, as
+// 16 columns' maxima grow in turn, cost 50 more instructions.
+// Timed in turn, before (all fp32 MFMA, copies through registers with the
+// 16-bit values widened, a rescale whenever a maximum grows) and now, in us:
+// causal bf16 16/2 heads, 1111 rows, D = 96 39 -> 22; D = 256 205 -> 43;
+// causal bf16 4 x 32/8, 2048 rows, D = 96 639 -> 223; decode bf16 16 x 32/8 x
+// 2048, D = 96 50 -> 25; causal fp32 16 heads, 777 rows, D = 64 27.5 -> 24.0,
+// D = 256 227 -> 82; fp32 2 heads, 128 rows, D = 64 7.7 -> 6.0.
+#include <type_traits>
+
 #include "fa_common.h"
 #include "fa_internal.h"
 
 namespace fa {
 namespace {
 
-constexpr int KB = 16;    // keys per wave and tile
 constexpr int QB = 16;    // query columns per wave
-constexpr int NWAVE = 8;  // waves per workgroup
-constexpr int NTH = 64 * NWAVE;
+constexpr int CUS = 256;  // compute units of the card
 
 struct GenericArgs {
     const void *q, *k, *v;
@@ -40,8 +57,10 @@ struct GenericArgs {
     float *lse;
     int B, Hq, Hkv, Nq, Nk, D;
     int causal;
-    float c;   // scale * log2(e), signed
+    float c;          // max(|scale|, tiny) * log2(e), > 0
+    unsigned qsign;   // sign bits of an element word, to negate q (scale < 0), else 0
     int nvb;   // blocks of 16 NSLOT columns per key/value head
+    Divisor per_vb, nkv, group;   // B * Hkv, Hkv, Hq / Hkv
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
 };
 
@@ -49,73 +68,157 @@ __device__ __forceinline__ float4_t mfma4(float a, float b, float4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Maxima without the quieting of signalling NaNs that the compiler adds (the
+// operands are results of arithmetic).
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float max_raw(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float quad_max(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return max_raw(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+// Reductions over the lane pair (l, l ^ 16), as pair_sum over (l, l ^ 32).
+__device__ __forceinline__ float half_sum(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Element types as the kernel uses them: the storage scalar, and for fp16 /
-// bf16 the operand type of the score product.
+// bf16 the operand type of the matrix products.
 template <typename T> struct Elem;
 template <> struct Elem<float> { typedef float scalar; };
 template <> struct Elem<f16_t> { typedef _Float16 scalar; };
 template <> struct Elem<bf16_t> { typedef __bf16 scalar; };
 
-// DP: D rounded up to a multiple of 32 (columns past D are zeros).
-template <typename TIN, int DP, int KSP> struct GSmem {
+// Two fp32 weights as three 16-bit terms each (t[0] + t[1] + t[2]).
+// bf16: the leading 8 bits are cut off three times: 24 bits, exact (the
+// remainder after a cut by a two-element dot product, p - 1 h_0 - 0 h_1 or
+// p - 0 h_0 - 1 h_1, which needs no shift; exact, checked on gfx950).
+__device__ __forceinline__ void split3(float p0, float p1, unsigned t[3], bf16_t) {
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    unsigned lo = 0x0000bf80u, hi = 0xbf800000u;   // (-1, 0) and (0, -1)
+    asm("" : "+s"(lo), "+s"(hi));   // in registers: as an inline operand -1.0 is not this pair
+    auto top = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
+    auto rest = [](unsigned h, unsigned one, float x) {
+        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, one), x, false);
+    };
+    t[0] = top(p0, p1);
+    const float m0 = rest(t[0], lo, p0), m1 = rest(t[0], hi, p1);
+    t[1] = top(m0, m1);
+    t[2] = top(rest(t[1], lo, m0), rest(t[1], hi, m1));
+}
+// fp16 (weights up to 2^15): 11 bits at a time, exact down to a last place of
+// 2^-24, that is 2^-39 of the largest weight.  The first term of a weight
+// that is not zero is kept from being zero, so that an infinite value shows.
+__device__ __forceinline__ void split3(float p0, float p1, unsigned t[3], f16_t) {
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    auto cut = [](float a, float b) { return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(a, b)); };
+    const us2 some = __builtin_elementwise_min(
+        __builtin_bit_cast(us2, __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u)), us2{1, 1});
+    const half2_t h = __builtin_bit_cast(half2_t, __builtin_elementwise_max(__builtin_bit_cast(us2, cut(p0, p1)), some));
+    auto rest_lo = [](unsigned h, float x) {   // x - h[0]
+        float r;
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+        return r;
+    };
+    auto rest_hi = [](unsigned h, float x) {   // x - h[1]
+        float r;
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+        return r;
+    };
+    t[0] = __builtin_bit_cast(unsigned, h);
+    const float m0 = rest_lo(t[0], p0), m1 = rest_hi(t[0], p1);
+    t[1] = __builtin_bit_cast(unsigned, cut(m0, m1));
+    t[2] = __builtin_bit_cast(unsigned, cut(rest_lo(t[1], m0), rest_hi(t[1], m1)));
+}
+
+constexpr int low_bit(int n, int cap) { return (n & -n) < cap ? (n & -n) : cap; }
+constexpr int log2i(int n) { return n > 1 ? 1 + log2i(n / 2) : 0; }
+
+// DP: D rounded up to a multiple of 32 (columns past D are zeros); NSLOT
+// blocks of 16 columns, KSP key parts, NB blocks of 16 keys per wave and tile.
+template <typename TIN, int DP, int NSLOT, int KSP, int NB> struct GCfg {
     static constexpr bool F32 = sizeof(typename Elem<TIN>::scalar) == 4;
-    static constexpr int NSLOT = NWAVE / KSP;
-    static constexpr int BC = KB * KSP;
-    // row strides: fp32 rows of DP + 4 words put the 16 rows of a 16-byte
-    // operand read, and the rows 4 apart of a value read, in different banks;
-    // 16-bit rows of DP + 8 do the same for the score operands
-    static constexpr int KS = F32 ? DP + 4 : DP + 8;
-    static constexpr int VS = DP + 4;
-    static constexpr int KBYTES = BC * KS * (F32 ? 4 : 2);
-    static constexpr int STAGE = KBYTES + BC * VS * 4;
-    static constexpr int NV = DP / 4 + 2;   // merge: accumulator, maximum and sum of a lane
+    static constexpr int ES = F32 ? 4 : 2;       // bytes per element
+    static constexpr int E = 16 / ES;            // elements per 16-byte chunk
+    static constexpr int CPR = DP / E;           // chunks per row
+    static constexpr int KB = 16 * NB, BC = KB * KSP;
+    static constexpr int NW = NSLOT * KSP;
+    static constexpr int KBYTES = BC * DP * ES;  // a K tile (V the same)
+    static constexpr int STAGE = 2 * KBYTES;
+    static constexpr int PIECES = KBYTES / 1024; // loads of 64 chunks per tile, K and V each
+    static constexpr int NP = (PIECES + NW - 1) / NW;
+    static constexpr int NV = DP / 4 + 2;        // merge: accumulator, maximum and sum of a lane
     static constexpr int MERGE = (KSP - 1) * NSLOT * NV * 64 * 4;
     static constexpr int BYTES = 2 * STAGE > MERGE ? 2 * STAGE : MERGE;   // two stages
+    // Swizzles: chunk c of row r is stored at chunk c ^ swz(r) of its row, so
+    // that the 16 rows of a 16-byte operand read, the eight rows (fp32: four)
+    // of a value read fall into different banks.
+    static constexpr int ZK = low_bit(CPR, 16), ZV = F32 ? low_bit(CPR / 4, 4) : low_bit(CPR / 2, 8);
+    static __device__ __forceinline__ int kswz(int r) { return (r >> (4 - log2i(ZK))) & (ZK - 1); }
+    static __device__ __forceinline__ int vswz(int r) {
+        return F32 ? ((r >> (2 - log2i(ZV))) & (ZV - 1)) << 2 : ((r >> (3 - log2i(ZV))) & (ZV - 1)) << 1;
+    }
+    static_assert(KBYTES % 1024 == 0 && (F32 || NB == 2), "tile shape");
 };
 
-template <typename TIN, typename TOUT, int DP, int KSP>
-__global__ __launch_bounds__(NTH) void generic_kernel(GenericArgs a) {
-    using SM = GSmem<TIN, DP, KSP>;
+template <typename TIN, typename TOUT, int DP, int NSLOT, int KSP, int NB>
+__global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a) {
+    using SM = GCfg<TIN, DP, NSLOT, KSP, NB>;
     typedef typename Elem<TIN>::scalar S;
-    constexpr bool F32 = SM::F32;
-    constexpr int NSLOT = SM::NSLOT, BC = SM::BC, KS = SM::KS, VS = SM::VS;
+    constexpr bool F32 = SM::F32, F16 = __is_same(TIN, f16_t);
+    constexpr int ES = SM::ES, E = SM::E, CPR = SM::CPR, KB = SM::KB, BC = SM::BC, NW = SM::NW, NP = SM::NP;
     constexpr int DT = DP / 16;                  // 16-column tiles of O
     constexpr bool VPRE = DP <= 128;             // value operands are read ahead of the softmax
-    constexpr int E = 16 / sizeof(S);            // elements per 16-byte chunk
-    constexpr int CPR = DP / E;                  // chunks per row
-    constexpr int NCH = (BC * CPR + NTH - 1) / NTH;   // chunks per thread, K and V each
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SM::BYTES];
-    auto ks_at = [&](int r) { return reinterpret_cast<S *>(smem + r * SM::STAGE); };
-    auto vs_at = [&](int r) { return reinterpret_cast<float *>(smem + r * SM::STAGE + SM::KBYTES); };
+    // partial sums of a score: fp32 takes D products in steps of four, one sum
+    // of 64 steps would round more than the scores of sharp softmaxes allow
+    constexpr int NSUM = !F32 ? 1 : DP <= 64 ? 2 : 4;
+    // The base of a column's weights moves (and its sums are rescaled) only
+    // when a score exceeds the largest one of that time by more than GROWTH;
+    // weights are at most 2^GROWTH, in fp16 2^15, for the range of their terms.
+    constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : 0.f;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[SM::BYTES];
 
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lc = l & 15, lg = l >> 4;
     const int slot = w % NSLOT, kp = w / NSLOT;
     // latest columns (most keys) first
-    const int per_vb = a.B * a.Hkv;
-    const int vb = a.nvb - 1 - (int)blockIdx.x / per_vb;
-    const int rest = (int)blockIdx.x % per_vb;
-    const int g = rest % a.Hkv, b = rest / a.Hkv;
-    const int G = a.Hq / a.Hkv, D = a.D, Nq = a.Nq;
-    const long long VR = (long long)Nq * G;      // columns of this key/value head
+    const int vb_r = (int)a.per_vb.div(blockIdx.x);
+    const int rest = (int)(blockIdx.x - vb_r * a.per_vb.d);
+    const int vb = a.nvb - 1 - vb_r;
+    const int b = (int)a.nkv.div(rest), g = rest - b * (int)a.nkv.d;
+    const int G = (int)a.group.d, D = a.D, Nq = a.Nq;
     // valid keys of this batch element (a.Nk rows per element in K and V)
-    const int Nk = a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk;
+    const int Nk = a.seqlens ? __builtin_amdgcn_readfirstlane(min(max(a.seqlens[b], 0), a.Nk)) : a.Nk;
     const int off = Nk - Nq;
-    const long long v_wg = (long long)vb * (QB * NSLOT), v_w = v_wg + slot * QB;
-    // row of a wave-uniform column (in 32 bits where the columns fit)
-    auto row_of = [&](long long v) { return VR <= 0x7fffffffLL ? (int)((unsigned)v / (unsigned)G) : (int)(v / G); };
-    const bool valid = v_w + lc < VR;
-    const int row_w = row_of(v_w);
-    const unsigned vrem = (unsigned)(v_w - (long long)row_w * G) + lc;   // < G + 16
-    const int row = row_w + (int)(vrem / (unsigned)G), h = g * G + (int)(vrem % (unsigned)G);
+    // Column t of the workgroup is column v0 + t of the key/value head: row
+    // row0 + (rem0 + t) / G, head (rem0 + t) % G of the group.
+    const long long v0 = (long long)vb * (QB * NSLOT);
+    const int row0 = v0 < 0x7fffffffLL ? (int)a.group.div((unsigned)v0) : (int)(v0 / G);
+    const unsigned rem0 = (unsigned)(v0 - (long long)row0 * G);
+    const int cols = (int)__builtin_elementwise_min((long long)Nq * G - v0, (long long)(QB * NSLOT));
+    auto row_of = [&](int t) { return row0 + (int)a.group.div(rem0 + t); };
+    const int t0 = QB * slot;
+    const bool valid = t0 + lc < cols;
+    const int row = row_of(t0 + lc), h = g * G + (int)(rem0 + t0 + lc - (unsigned)(row - row0) * (unsigned)G);
 
     // Key extents: workgroup, wave, keys that every column of the wave sees,
     // and this lane's column (bottom-right causal alignment).
     auto extent = [&](int i) { return a.causal ? min(Nk, i + off + 1) : Nk; };
-    const int kend_wg = extent(row_of(__builtin_elementwise_min(v_wg + QB * NSLOT, VR) - 1));
-    const int kend_w = v_w < VR ? extent(row_of(__builtin_elementwise_min(v_w + QB, VR) - 1)) : 0;
-    const int kfree_w = v_w < VR ? extent(row_w) : 0;
+    const int kend_wg = extent(row_of(cols - 1));
+    const int kend_w = t0 < cols ? extent(row_of(min(t0 + QB, cols) - 1)) : 0;
+    const int kfree_w = t0 < cols ? extent(row_of(t0)) : 0;
     const int myend = extent(row);
 
     // Q operand: fp32, chunk i holds columns 16 i + 4 lg .. + 3; 16-bit, k-step
@@ -128,137 +231,201 @@ __global__ __launch_bounds__(NTH) void generic_kernel(GenericArgs a) {
         for (int i = 0; i < NQF; ++i) {
             const int d = 4 * E * i + E * lg;
             qf[i] = uint4_t{0u, 0u, 0u, 0u};
-            if (valid && d < D) qf[i] = ld16(qp + d);
+            if (valid && d < D) qf[i] = ld16(qp + d) ^ a.qsign;
         }
     }
 
-    // Tile staging: chunk e = tid + NTH c is key e / CPR, 16-byte chunk e % CPR;
-    // columns past D and keys past the end read as zero.
-    uint4_t kr[NCH], vr[NCH];
-    const size_t kv0 = ((size_t)b * a.Nk * a.Hkv + g) * D;
-    auto load_tile = [&](int k0) {
+    // Tile staging, memory to LDS directly: piece j of a tile is its chunks
+    // 64 j .. 64 j + 63, lane l's the l-th; chunks past D and keys past the
+    // end (past the view's) become zeros.
+    const long long pitch = (long long)a.Hkv * D * ES;   // bytes between consecutive keys
+    const bool far = pitch * BC > 0x7fffffffLL;          // a tile's offsets exceed a buffer view's 31 bits
+    int koff[NP], voff[NP];
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int e = tid + NTH * c, key = k0 + e / CPR, d = E * (e % CPR);
-            kr[c] = uint4_t{0u, 0u, 0u, 0u};
-            vr[c] = uint4_t{0u, 0u, 0u, 0u};
-            if (e < BC * CPR && key < Nk && d < D) {
-                const size_t o = kv0 + (size_t)key * a.Hkv * D + d;
-                kr[c] = ld16(reinterpret_cast<const S *>(a.k) + o);
-                vr[c] = ld16(reinterpret_cast<const S *>(a.v) + o);
-            }
-        }
-    };
-    auto store_tile = [&](int r) {
-        S *ks = ks_at(r);
-        float *vs = vs_at(r);
+    for (int j = 0; j < NP; ++j) {
+        const int e = 64 * (w + NW * j) + l, r = e / CPR, c = e % CPR;
+        const int ck = c ^ SM::kswz(r), cv = c ^ SM::vswz(r);
+        koff[j] = E * ck < D ? r * (int)pitch + 16 * ck : (int)0x80000000;
+        voff[j] = E * cv < D ? r * (int)pitch + 16 * cv : (int)0x80000000;
+    }
+    const unsigned lds0 = lds_address(smem);
+    const size_t head0 = ((size_t)b * a.Nk * a.Hkv + g) * (size_t)D * ES;
+    const char *ktile = reinterpret_cast<const char *>(a.k) + head0;
+    const char *vtile = reinterpret_cast<const char *>(a.v) + head0;
+    long long left = (long long)(Nk - 1) * pitch + D * ES;   // bytes from the next tile's first key to the last one's end
+    auto load_tile = [&](int k0, int st) {   // tiles are loaded in order
+        if (!far) {
+            const int nrec = (int)__builtin_elementwise_min(left, 0x7fffffffLL);
+            const unsigned dst = lds0 + st * SM::STAGE + 1024 * w;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int e = tid + NTH * c, key = e / CPR, d = E * (e % CPR);
-            if (BC * CPR % NTH == 0 || e < BC * CPR) {
-                st16(ks + key * KS + d, kr[c]);
-                if constexpr (F32) {
-                    st16(vs + key * VS + d, vr[c]);
-                } else {
-                    typedef S s8 __attribute__((ext_vector_type(8)));
-                    const s8 x = __builtin_bit_cast(s8, vr[c]);
-                    *reinterpret_cast<float4_t *>(vs + key * VS + d) =
-                        float4_t{to_f32(x[0]), to_f32(x[1]), to_f32(x[2]), to_f32(x[3])};
-                    *reinterpret_cast<float4_t *>(vs + key * VS + d + 4) =
-                        float4_t{to_f32(x[4]), to_f32(x[5]), to_f32(x[6]), to_f32(x[7])};
+            for (int j = 0; j < NP; ++j)
+                if (SM::PIECES % NW == 0 || w + NW * j < SM::PIECES) load_lds16(ktile, nrec, dst + 1024 * NW * j, koff[j]);
+#pragma unroll
+            for (int j = 0; j < NP; ++j)
+                if (SM::PIECES % NW == 0 || w + NW * j < SM::PIECES)
+                    load_lds16(vtile, nrec, dst + SM::KBYTES + 1024 * NW * j, voff[j]);
+        } else {   // the same through registers, with 64-bit offsets
+            for (int e = tid; e < BC * CPR; e += 64 * NW) {
+                const int r = e / CPR, c = e % CPR;
+                uint4_t kc = uint4_t{0u, 0u, 0u, 0u}, vc = kc;
+                if (k0 + r < Nk && E * c < D) {
+                    kc = ld16(ktile + r * pitch + 16 * c);
+                    vc = ld16(vtile + r * pitch + 16 * c);
                 }
+                unsigned char *row_at = smem + st * SM::STAGE + r * (DP * ES);
+                st16(row_at + 16 * (c ^ SM::kswz(r)), kc);
+                st16(row_at + SM::KBYTES + 16 * (c ^ SM::vswz(r)), vc);
             }
         }
+        ktile += BC * pitch;
+        vtile += BC * pitch;
+        left -= BC * pitch;
     };
 
-    float4_t oacc[DT];
+    // Accumulators.  16-bit inputs: the weights' first terms in oacc, the
+    // others in olow (apart, so that an infinite value, times a zero term,
+    // does not turn into NaN).
+    float4_t oacc[DT], olow[F32 ? 1 : DT];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) oacc[dt] = float4_t{};
-    float m = -INFINITY;   // running maximum of the column (log2 domain), the same in its four lanes
+    for (int dt = 0; dt < DT; ++dt) {
+        oacc[dt] = float4_t{};
+        if constexpr (!F32) olow[dt] = float4_t{};
+    }
+    // Base of the column's weights (log2 domain; the same in its four lanes)
+    // and the largest score it is kept for; no score seen yet: 0 and -inf.
+    float base = 0.f, lim = -INFINITY;
     float lsum = 0.f;      // this lane's part of the sum
 
-    auto block = [&](int kb, const S *ks, const float *vs) {   // the wave's 16 keys of a tile
+    // Lane constants of the operand reads.  Key of a lane's score 4 j + r:
+    // 16 j + 4 lg + r, in fp32 (rows of K read in the order 4 (i % 4) + i / 4)
+    // 16 j + 4 r + lg, so that the four rows of a value read are consecutive.
+    const int krow = KB * kp + (F32 ? 4 * (lc & 3) + (lc >> 2) : lc);
+    const int vrow = KB * kp + (F32 ? lg : 4 * lg + (lc >> 2));
+    auto block = [&](int kb, const unsigned char *ks) {   // the wave's KB keys of a tile
+        const unsigned char *vs = ks + SM::KBYTES;
 
-        // ---- scores: lane holds keys kb + 4 lg + r of column lc
-        float4_t s0 = float4_t{}, s1 = float4_t{};
-        const S *kl = ks + (KB * kp + lc) * KS + E * lg;
+        // ---- scores
+        float x[4 * NB];
 #pragma unroll
-        for (int i = 0; i < NQF; ++i) {
-            const uint4_t ku = *reinterpret_cast<const uint4_t *>(kl + 4 * E * i);
-            if constexpr (F32) {
-                const float4_t kf = __builtin_bit_cast(float4_t, ku), q4 = __builtin_bit_cast(float4_t, qf[i]);
-                s0 = mfma4(kf[0], q4[0], s0);
-                s1 = mfma4(kf[1], q4[1], s1);
-                s0 = mfma4(kf[2], q4[2], s0);
-                s1 = mfma4(kf[3], q4[3], s1);
-            } else {
-                typedef typename TIN::vec8 V8;
-                s0 = mfma16(as_vec8<V8>(ku), as_vec8<V8>(qf[i]), s0);
+        for (int j = 0; j < NB; ++j) {
+            float4_t sc[NSUM];
+#pragma unroll
+            for (int n = 0; n < NSUM; ++n) sc[n] = float4_t{};
+            const unsigned char *kl = ks + (krow + 16 * j) * (DP * ES);
+#pragma unroll
+            for (int i = 0; i < NQF; ++i) {
+                const uint4_t ku = *reinterpret_cast<const uint4_t *>(kl + 16 * ((4 * i + lg) ^ SM::kswz(krow)));
+                if constexpr (F32) {
+                    const float4_t kf = __builtin_bit_cast(float4_t, ku), q4 = __builtin_bit_cast(float4_t, qf[i]);
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) sc[n % NSUM] = mfma4(kf[n], q4[n], sc[n % NSUM]);
+                } else {
+                    typedef typename TIN::vec8 V8;
+                    sc[0] = mfma16(as_vec8<V8>(ku), as_vec8<V8>(qf[i]), sc[0]);
+                }
             }
-        }
-        float x[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = (F32 ? s0[r] + s1[r] : s0[r]) * a.c;
+            for (int r = 0; r < 4; ++r) x[4 * j + r] = NSUM == 4 ? (sc[0][r] + sc[NSUM > 1 ? 1 : 0][r]) + (sc[NSUM - 2][r] + sc[NSUM - 1][r]) : NSUM == 2 ? sc[0][r] + sc[NSUM > 1 ? 1 : 0][r] : sc[0][r];
+        }
         if (kb + KB > kfree_w) {   // wave-uniform: some column does not see all of them
 #pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = kb + 4 * lg + r < myend ? x[r] : -INFINITY;
+            for (int i = 0; i < 4 * NB; ++i)
+                x[i] = kb + 16 * (i / 4) + (F32 ? 4 * (i % 4) + lg : 4 * lg + i % 4) < myend ? x[i] : -INFINITY;
         }
 
         // value operands, ahead of the softmax
-        const float *vl = vs + (KB * kp + 4 * lg) * VS + lc;
-        float va[4][DT];
-        if constexpr (VPRE) {   // (up to 32 registers)
+        typedef typename std::conditional<F32, float, uint4_t>::type vop_t;
+        constexpr int NVO = F32 ? 4 * NB : 1;    // operands per column tile
+        auto vread = [&](int i, int dt) {
+            if constexpr (F32) {
+                return *reinterpret_cast<const float *>(vs + (vrow + 16 * (i / 4) + 4 * (i % 4)) * (DP * ES) +
+                                                        64 * (dt ^ (SM::vswz(vrow + 4 * (i % 4)) >> 2)) + 4 * lc);
+            } else {
+                const _Float16 *p = reinterpret_cast<const _Float16 *>(vs + vrow * (DP * ES) + 32 * (dt ^ (SM::vswz(vrow) >> 1)) + 8 * (lc & 3));
+                return __builtin_bit_cast(uint4_t, cat_half8(lds_read_tr16(p), lds_read_tr16(p + 16 * DP)));
+            }
+        };
+        vop_t va[NVO][DT];
+        if constexpr (VPRE) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < NVO; ++i)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) va[r][dt] = vl[r * VS + 16 * dt];
+                for (int dt = 0; dt < DT; ++dt) va[i][dt] = vread(i, dt);
         }
 
         // ---- streaming softmax
-        float mx = __builtin_fmaxf(__builtin_fmaxf(x[0], x[1]), __builtin_fmaxf(x[2], x[3]));
-        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 16));
-        mx = pair_max(mx);
-        const float m_new = __builtin_fmaxf(m, mx);
-        if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-            const float alpha = (m == -INFINITY) ? 0.f : exp2_fast(m - m_new);
-            m = m_new;
+        float mx = max3_raw(x[0], x[1], x[2]);
+#pragma unroll
+        for (int i = 3; i + 1 < 4 * NB; i += 2) mx = max3_raw(mx, x[i], x[i + 1]);
+        mx = quad_max(max_raw(mx, x[4 * NB - 1])) * a.c;
+        if (__builtin_amdgcn_ballot_w64(mx > lim)) {
+            const bool over = mx > lim;
+            const float b_new = over ? mx - HEADROOM : base;
+            const float alpha = lim == -INFINITY ? 0.f : exp2_fast(base - b_new);
+            base = b_new;
+            if (over) lim = mx + GROWTH;
             lsum *= alpha;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
+            for (int dt = 0; dt < DT; ++dt) {
+                oacc[dt] *= alpha;
+                if constexpr (!F32) olow[dt] *= alpha;
+            }
         }
-        float p[4];
+        float p[4 * NB];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = (x[r] == -INFINITY) ? 0.f : exp2_fast(x[r] - m);
-        lsum += (p[0] + p[1]) + (p[2] + p[3]);
+        for (int i = 0; i < 4 * NB; ++i) p[i] = exp2_fast(__builtin_fmaf(x[i], a.c, -base));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) lsum += (p[4 * j] + p[4 * j + 1]) + (p[4 * j + 2] + p[4 * j + 3]);
 
-        // ---- values: step r multiplies keys kb + 4 lg + r of all lane groups
+        // ---- values
+        if constexpr (F32) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+            for (int i = 0; i < 4 * NB; ++i)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) oacc[dt] = mfma4(VPRE ? va[r][dt] : vl[r * VS + 16 * dt], p[r], oacc[dt]);
+                for (int dt = 0; dt < DT; ++dt) oacc[dt] = mfma4(VPRE ? va[i][dt] : vread(i, dt), p[i], oacc[dt]);
+        } else {
+            typedef typename TIN::vec8 V8;
+            uint4_t pt[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                unsigned t[3];
+                split3(p[2 * i], p[2 * i + 1], t, TIN());
+#pragma unroll
+                for (int n = 0; n < 3; ++n) pt[n][i] = t[n];
+            }
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const V8 vv = as_vec8<V8>(VPRE ? va[0][dt] : vread(0, dt));
+                oacc[dt] = mfma16(vv, as_vec8<V8>(pt[0]), oacc[dt]);
+                olow[dt] = mfma16(vv, as_vec8<V8>(pt[1]), olow[dt]);
+                olow[dt] = mfma16(vv, as_vec8<V8>(pt[2]), olow[dt]);
+            }
         }
     };
 
-    if (kend_wg > 0) {
-        load_tile(0);
-        store_tile(0);
-    }
-    // Q has arrived here, so that no wait for it stands in the loop (where it
-    // would also cover the loads of the next tile)
+    if (kend_wg > 0) load_tile(0, 0);
+    // Q has arrived here, so that no wait for it stands in the loop
 #pragma unroll
     for (int i = 0; i < NQF; ++i) asm volatile("" : "+v"(qf[i]));
-    __syncthreads();
     for (int k0 = 0, st = 0; k0 < kend_wg; k0 += BC, st ^= 1) {
-        const bool more = k0 + BC < kend_wg;
-        if (more) load_tile(k0 + BC);
+        lds_loads_done<0>();
+        lds_barrier();
+        if (k0 + BC < kend_wg) load_tile(k0 + BC, st ^ 1);
         const int kb = k0 + KB * kp;
-        if (kb < kend_w) block(kb, ks_at(st), vs_at(st));   // else no column sees these keys (wave-uniform)
-        if (more) store_tile(st ^ 1);
-        __syncthreads();
+        if (kb < kend_w) block(kb, smem + st * SM::STAGE);   // else no column sees these keys (wave-uniform)
+    }
+    float m = lim == -INFINITY ? -INFINITY : base;
+    if constexpr (!F32) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)   // (the first terms' sum alone where it is not finite)
+                oacc[dt][r] = oacc[dt][r] - oacc[dt][r] == 0.f ? oacc[dt][r] + olow[dt][r] : oacc[dt][r];
     }
 
     // ---- merge the key parts of each slot through LDS
     if constexpr (KSP > 1) {
+        lds_barrier();
         constexpr int NV = SM::NV;
         float *mf = reinterpret_cast<float *>(smem) + l;
         if (kp > 0) {
@@ -292,8 +459,7 @@ __global__ __launch_bounds__(NTH) void generic_kernel(GenericArgs a) {
         }
         m = M;
     }
-    lsum += __shfl_xor(lsum, 16);
-    lsum = pair_sum(lsum);
+    lsum = pair_sum(half_sum(lsum));
     if (!valid) return;
     const float inv = lsum > 0.f ? 1.f / lsum : 0.f;   // no visible key: 0
     TOUT *op = reinterpret_cast<TOUT *>(a.o) + ((size_t)((size_t)b * Nq + row) * a.Hq + h) * D;
@@ -312,32 +478,64 @@ __global__ __launch_bounds__(NTH) void generic_kernel(GenericArgs a) {
         a.lse[((size_t)b * a.Hq + h) * Nq + row] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
 }
 
-template <typename TIN, typename TOUT, int DP, int KSP>
+template <typename TIN, typename TOUT, int DP, int NSLOT, int KSP, int NB>
 hipError_t launch_t(const Problem &p, hipStream_t stream) {
     GenericArgs a;
     a.q = p.q; a.k = p.k; a.v = p.v; a.o = p.o; a.lse = p.lse;
     a.B = p.B; a.Hq = p.Hq; a.Hkv = p.Hkv; a.Nq = p.Nq; a.Nk = p.Nk; a.D = p.D;
     a.causal = p.causal;
     a.seqlens = p.seqlens;
-    a.c = p.scale * kLog2e;
-    constexpr int COLS = QB * NWAVE / KSP;
+    // A zero scale keeps a tiny positive factor, for masked scores of -inf.
+    a.c = __builtin_fmaxf(__builtin_fabsf(p.scale), 1e-30f) * kLog2e;
+    a.qsign = p.scale < 0.f ? (sizeof(typename Elem<TIN>::scalar) == 4 ? 0x80000000u : 0x80008000u) : 0u;
+    constexpr int COLS = QB * NSLOT;
     const long long nvb = ((long long)p.Nq * (p.Hq / p.Hkv) + COLS - 1) / COLS;
     const long long nblocks = nvb * p.B * p.Hkv;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.nvb = (int)nvb;
-    hipLaunchKernelGGL((generic_kernel<TIN, TOUT, DP, KSP>), dim3((unsigned)nblocks), dim3(NTH), 0, stream, a);
+    a.per_vb = Divisor((unsigned)p.B * p.Hkv);   // <= nblocks
+    a.nkv = Divisor(p.Hkv);
+    a.group = Divisor(p.Hq / p.Hkv);
+    hipLaunchKernelGGL((generic_kernel<TIN, TOUT, DP, NSLOT, KSP, NB>), dim3((unsigned)nblocks), dim3(64 * NSLOT * KSP), 0, stream, a);
     return hipGetLastError();
 }
 
-// Key parts: four where two stages of 64 keys leave room for a second
-// workgroup on the CU (or nearly: D = 128 in fp32 takes 135 KB), fewer for
-// wider rows.  Fewer parts mean longer waves: with two at D = 64 the 16-head,
-// 777-row causal fp32 call took 38 us against 27, at D = 96 the 16/2-head,
-// 1111-row bf16 call 51 against 37; with eight the 777-row call took 34 (each
-// staged tile then serves half the columns).
+// Layouts (column blocks, key parts).  A tile staged for more columns costs
+// less per column; more key parts, and more workgroups of fewer columns,
+// shorten the longest chain of steps.  So: small workgroups while they all
+// start at once (a causal call of about square shape: twice as many, the
+// second half being short), large ones for grids that fill the card anyway.
+// In us, on both sides of each line:
+//   fp32, up to 128 columns: (1, 4) against (2, 4): 16 heads, 777 rows causal,
+//     D = 64 25.4 / 26.4; decode 16 x 32/8 x 2048, D = 64 36.6 / 47.8; past
+//     the line, 2/8 heads x 1000, D = 96 53.9 / 38.3, 4 x 32/8 x 1024 causal,
+//     D = 64 230 / 174
+//   16 bits, up to 128: (2, 4) against (4, 2): 16 x 512, D = 80 10.3 / 13.6;
+//     16/2 x 100 against 4000, D = 96 37 / 66; 32/8 x 2048 causal, D = 96
+//     95 / 63
+//   fp32, above 128: (2, 2) against (4, 2): 16 x 777 causal, D = 192 63 / 88;
+//     16 x 1024, D = 192 152 / 118
+//   above 128, (4, 2) against (8, 1): bf16 16/2 x 1111 causal, D = 256
+//     43 / 66; with a workgroup of (8, 1) for every CU, 32/8 x 1024, D = 256
+//     81 / 70, fp32 32 x 1024, D = 192 223 / 211 (but D = 160, 2 x 32 x 1024
+//     causal 219 / 241)
 template <typename TIN, typename TOUT, int DP>
 hipError_t launch_k(const Problem &p, hipStream_t s) {
-    return launch_t<TIN, TOUT, DP, DP <= 128 ? 4 : DP <= 160 ? 2 : 1>(p, s);
+    constexpr bool F32 = sizeof(typename Elem<TIN>::scalar) == 4, WIDE = DP > 128;
+    constexpr int NB = F32 ? 1 : 2;
+    const long long cols = (long long)p.Nq * (p.Hq / p.Hkv), kvheads = (long long)p.B * p.Hkv;
+    auto groups = [&](int ns) { return (cols + QB * ns - 1) / (QB * ns) * kvheads; };   // workgroups of ns blocks
+    if constexpr (F32 || !WIDE) {
+        constexpr int NS = F32 && !WIDE ? 1 : 2, KSP = WIDE ? 2 : 4;
+        constexpr int FIT = 163840 / GCfg<TIN, DP, NS, KSP, NB>::BYTES;   // workgroups per CU by LDS
+        const int rounds = p.causal && p.Nk < 2LL * p.Nq ? 2 : 1;
+        if (groups(NS) <= CUS * (FIT < 2 ? FIT : 2) * rounds) return launch_t<TIN, TOUT, DP, NS, KSP, NB>(p, s);
+    }
+    if constexpr (WIDE && !(F32 && DP == 160)) {
+        if (groups(8) >= CUS) return launch_t<TIN, TOUT, DP, 8, 1, NB>(p, s);
+    }
+    if constexpr (F32 && !WIDE) return launch_t<TIN, TOUT, DP, 2, 4, NB>(p, s);
+    else return launch_t<TIN, TOUT, DP, 4, 2, NB>(p, s);
 }
 
 template <typename TIN, typename TOUT>
