@@ -200,4 +200,37 @@ struct Divisor {
     __device__ __forceinline__ unsigned div(unsigned n) const { return (unsigned)(((unsigned long long)n * m) >> shift); }
 };
 
+// Sequences by length, at most kMaxRanked of them, one per lane.  uneven: some
+// sequence is shorter than 7/8 of the longest.  nth_longest: the batch element
+// with the r-th largest length (0: the longest; equal ones in order); each lane
+// ranks one element against the others.
+constexpr int kMaxRanked = 64;
+struct Lengths {
+    int len, B, lane;
+    __device__ __forceinline__ Lengths(const int *seqlens, int b, int l) : B(b), lane(l) {
+        len = seqlens[min(l, b - 1)];
+    }
+    __device__ __forceinline__ bool uneven() const {
+        const int n = max(len, 0);
+        int mx = n;   // over the wave: lanes ^ 1, ^ 2, the other half of 8, of 16, lanes ^ 16, ^ 32
+        mx = max(mx, __builtin_amdgcn_mov_dpp(mx, 0xb1, 0xf, 0xf, true));
+        mx = max(mx, __builtin_amdgcn_mov_dpp(mx, 0x4e, 0xf, 0xf, true));
+        mx = max(mx, __builtin_amdgcn_mov_dpp(mx, 0x141, 0xf, 0xf, true));
+        mx = max(mx, __builtin_amdgcn_mov_dpp(mx, 0x140, 0xf, 0xf, true));
+        auto r = __builtin_amdgcn_permlane16_swap(mx, mx, false, false);
+        mx = max((int)r[0], (int)r[1]);
+        auto q = __builtin_amdgcn_permlane32_swap(mx, mx, false, false);
+        mx = max((int)q[0], (int)q[1]);
+        return __builtin_amdgcn_ballot_w64(n < mx - (mx >> 3)) != 0;
+    }
+    __device__ __forceinline__ int nth_longest(int r) const {
+        const unsigned key = (unsigned)min(max(len, 0), 0x3ffffff) << 6 | (63 - lane);   // all different
+        int rank = 0;
+#pragma unroll 4
+        for (int i = 0; i < B; ++i) rank += (unsigned)__builtin_amdgcn_readlane(key, i) > key;
+        return __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < B && rank == r));
+    }
+    __device__ __forceinline__ int of(int b) const { return __builtin_amdgcn_readlane(len, b); }
+};
+
 }  // namespace fa

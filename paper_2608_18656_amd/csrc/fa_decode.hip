@@ -56,6 +56,8 @@ struct DecodeArgs {
     Divisor S;      // splits
     Divisor nqg;    // 16-head query groups per key/value head
     Divisor nkv;    // key/value heads
+    int B, ranked;  // ranked > 0: uneven sequences are taken by length, the first `ranked`
+                    // longest first, the others shortest first
     float c;        // |scale| * log2(e)
     unsigned qsign; // sign flip of q for negative scale
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
@@ -98,11 +100,23 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
     const int bid = blockIdx.x;
     const int u = a.S.div(bid), s = bid - u * a.S.d;
     const int u2 = a.nqg.div(u), qg = u - u2 * a.nqg.d;
-    const int b = a.nkv.div(u2), g = u2 - b * a.nkv.d;
+    int b = a.nkv.div(u2), len = a.Nk;
+    const int g = u2 - b * a.nkv.d;
+    // Sequences of uneven length, in grids past one workgroup per CU: longest
+    // first, so that the last round is short (64 x 32/8 heads, 512 to 4096 keys,
+    // D = 128 119 -> 103 us; 40 of them, D = 64 39.4 -> 36.2); when all start at
+    // once, one workgroup for every CU, the others shortest first
+    if (a.ranked > 0) {
+        const Lengths lens(a.seqlens, a.B, l);
+        if (lens.uneven()) b = lens.nth_longest(b < a.ranked ? b : a.B - 1 - (b - a.ranked));
+        len = lens.of(b);
+    } else if (a.seqlens) {
+        len = a.seqlens[b];
+    }
     const int G = a.G;
     // valid keys of this batch element (a cache of a.Nk rows per element), and
     // its split: the sequence's own keys, spread evenly in multiples of KPW
-    const int Nk = __builtin_amdgcn_readfirstlane(a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk);
+    const int Nk = __builtin_amdgcn_readfirstlane(min(max(len, 0), a.Nk));
     const unsigned whole = a.S.div(Nk), per = whole + (whole * a.S.d != (unsigned)Nk);   // ceil(Nk / S)
     const long long chunk = (per + (KPW - 1)) & ~(unsigned)(KPW - 1);
     const int k0 = (int)min(s * chunk, (long long)Nk);
@@ -365,6 +379,9 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(const float *__restri
     if (lse && t == 0) lse[bh] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
+// Workgroups that the chip holds at once.
+constexpr long long resident(int D) { return D == 64 ? 2 * CUS : CUS; }
+
 template <typename TIN, typename TOUT, int D>
 hipError_t launch_t(const Problem &p, int S, void *ws, hipStream_t stream) {
     DecodeArgs a;
@@ -391,6 +408,12 @@ hipError_t launch_t(const Problem &p, int S, void *ws, hipStream_t stream) {
     a.num_pages = p.num_pages;
     const long long nblocks = (long long)p.B * p.Hkv * nqg * S;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    a.B = p.B;
+    a.ranked = 0;
+    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > CUS) {
+        const long long per_seq = nblocks / p.B;
+        a.ranked = nblocks <= resident(D) ? (int)((CUS + per_seq - 1) / per_seq) : p.B;
+    }
     if (p.block_table)
         hipLaunchKernelGGL((decode_split_kernel<TIN, D, true>), dim3((unsigned)nblocks), dim3(64 * NW), 0,
                            stream, a);
@@ -434,7 +457,7 @@ int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D) {
     const long long units = (long long)B * Hkv * ((G + QG - 1) / QG);
     long long cap = (Nk + (long long)MIN_KEYS_PER_SPLIT - 1) / MIN_KEYS_PER_SPLIT;
     if (cap > FA_MAX_SPLITS) cap = FA_MAX_SPLITS;
-    const long long slots = D == 64 ? 2 * CUS : CUS;   // workgroups the chip holds
+    const long long slots = resident(D);
     long long best = 1, least = 0;
     for (int j = 0; j <= MAX_ROUNDS; ++j) {
         long long S = j == 0 ? 1 : j * (long long)CUS / units;

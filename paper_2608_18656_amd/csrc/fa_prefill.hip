@@ -81,7 +81,11 @@ struct PrefillArgs {
     Divisor per_mb;   // workgroups per row block: B * Hkv * (G / HW)
     Divisor nhg;      // head groups per key/value head (G / HW)
     Divisor nkv;      // key/value heads
-    int pair;         // 1: every workgroup is resident at once; order heavy/light pairs
+    int ranked;       // > 0: uneven sequences are taken by length, the first `ranked` of their row
+                      // blocks longest first, the others shortest first
+    Divisor per_seq;      // workgroups per sequence and row block: Hkv * (G / HW)
+    Divisor row_blocks;   // nmb
+    int first;        // row blocks taken longest first, the others shortest first
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
     const int *block_table;   // paged K/V: page of each key block (see Problem)
     int page_size, max_pages, num_pages;
@@ -144,15 +148,39 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     const int bid = blockIdx.x;
     // Row block of this workgroup.  Latest rows (most keys) first, so that
     // the short causal blocks fill the tail; when the whole grid is resident
-    // at once (two workgroups per CU), the first half of the grid takes the
-    // long blocks in decreasing and the second half the short ones in
-    // increasing length, so that the two workgroups sharing a CU carry about
-    // the same total work.
-    const int q_ = a.per_mb.div(bid), half_ = (a.nmb + 1) / 2;
-    const int mb = (!a.pair || q_ < half_) ? a.nmb - 1 - q_ : q_ - half_;
-    const int rest = bid - q_ * a.per_mb.d;
+    // at once, only one workgroup for every CU in that order and the others
+    // shortest first, so that workgroups sharing a CU carry about the same
+    // total work (one per CU rather than half of the grid, us: 32/8 heads,
+    // D = 64, 1200 rows 21.9 -> 20.1; D = 128, 1100 rows 30.6 -> 29.0, 3000 rows
+    // 93.5 -> 89.7).  With lengths of their own that differ, sequences are
+    // taken by length and rows within them, in that same pattern: in the order
+    // of the batch two workgroups of one sequence share a CU, and the CUs of the
+    // long ones finish last (4 x 32/8 heads, 512 rows, 4096 to 1024 keys, D = 64
+    // 68 -> 54; 16 such sequences 250 -> 210; 6 of 1024 rows, D = 128 288 -> 250).
+    // About equal ones stay in the order of the batch, where workgroups that
+    // share a CU share its L1 as well (4 x 4096 keys 83 against 86 by rank).
+    const int q_ = a.per_mb.div(bid);
+    int mb = q_ < a.first ? a.nmb - 1 - q_ : q_ - a.first;
+    int rest = bid - q_ * a.per_mb.d;
+    int b = -1, len = a.Nk;
+    if (a.ranked > 0) {
+        const Lengths lens(a.seqlens, a.B, l);
+        if (lens.uneven()) {
+            const int u = a.per_seq.div(bid);
+            rest = bid - u * a.per_seq.d;
+            const int j = u < a.ranked ? u : a.B * a.nmb - 1 - (u - a.ranked), r = a.row_blocks.div(j);
+            mb = a.nmb - 1 - (j - r * a.nmb);
+            b = lens.nth_longest(r);
+        }
+        if (b < 0) b = a.nkv.div(a.nhg.div(rest));
+        len = lens.of(b);
+    }
     const int bg = a.nhg.div(rest), hg = rest - bg * a.nhg.d;
-    const int b = a.nkv.div(bg), g = bg - b * a.nkv.d;
+    const int b0 = a.nkv.div(bg), g = bg - b0 * a.nkv.d;
+    if (a.ranked == 0) {
+        b = b0;
+        if (a.seqlens) len = a.seqlens[b];
+    }
     const int G = a.G;
     const int hs = slot & (a.HW - 1), rs = slot >> a.lgHW;
     const int h = g * G + hg * a.HW + hs;
@@ -163,7 +191,7 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // Valid keys of this batch element: with per-sequence lengths the K/V
     // tensors hold a.Nk rows per batch element of which the first seqlens[b]
     // are valid, and the queries are the sequence's last Nq positions.
-    const int Nk = __builtin_amdgcn_readfirstlane(a.seqlens ? min(max(a.seqlens[b], 0), a.Nk) : a.Nk);
+    const int Nk = __builtin_amdgcn_readfirstlane(min(max(len, 0), a.Nk));
     const int off = Nk - Nq;
 
     // Key extents: workgroup, this slot, and keys every row of the slot sees.
@@ -628,7 +656,6 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.HW = p.hw > 0 ? p.hw : hw;
     const int RB = NS / a.HW;
     a.nmb = (p.Nq + WR * RB - 1) / (WR * RB);
-    a.pair = 0;
     const long long nblocks = (long long)a.nmb * p.B * p.Hkv * (G / a.HW);
     if (nblocks <= 0) return hipSuccess;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
@@ -637,7 +664,16 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.nhg = Divisor(G / a.HW);
     a.nkv = Divisor(p.Hkv);
     a.per_mb = Divisor((unsigned)p.B * p.Hkv * (G / a.HW));   // <= nblocks
-    if (p.causal) a.pair = nblocks <= (long long)SM::WPC * cu_count() ? 1 : 0;
+    const int cus = cu_count();
+    const bool at_once = nblocks <= (long long)SM::WPC * cus;   // every workgroup is resident from the start
+    a.first = p.causal && at_once ? (cus + (int)a.per_mb.d - 1) / (int)a.per_mb.d : a.nmb;
+    a.ranked = 0;
+    a.row_blocks = Divisor(a.nmb);
+    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > cus) {
+        const int per_seq = p.Hkv * (G / a.HW);
+        a.per_seq = Divisor(per_seq);
+        a.ranked = at_once ? (cus + per_seq - 1) / per_seq : a.nmb * p.B;
+    }
     if constexpr (NS == NSLOT) {
         if (p.block_table) {
             hipLaunchKernelGGL((prefill_kernel<TIN, TOUT, D, NS, CAUSAL, true>), dim3((unsigned)nblocks),
