@@ -255,20 +255,23 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     int tload = 0;
     // paged K/V: the pool of pages, at head g.  Tiles are loaded in order
     // and a page holds a whole number of tiles, so the page index and the
-    // offset inside the page advance without a division.  The table entry of
-    // the following page is read ahead with a vector load through a view of
-    // this sequence's row of the table (entries past the row read as zero),
-    // so it has arrived when the page is reached, and no scalar load (whose
-    // counter the LDS reads share) is in flight during a step.
+    // offset inside the page advance without a division.  The wave holds 64
+    // table entries, one per lane, and the next 64, read with vector loads
+    // through a view of this sequence's row of the table (entries past the row
+    // read as zero): no scalar load (whose counter the LDS reads share) is in
+    // flight during a step, and no wait for an entry stands between the loads
+    // of two tiles, where it would wait for the tiles as well (with the entry
+    // of the following page loaded alone, 5 x 32/4 heads, 61 rows, 7680 keys,
+    // D = 64, pages of 64 took 115 us against 78 for contiguous keys).
     const __amdgpu_buffer_rsrc_t trs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int *>(PAGED ? a.block_table + (size_t)b * a.max_pages : nullptr), (short)0,
         PAGED ? a.max_pages * 4 : 0, 0x00020000);
     const size_t page_elems = (size_t)a.page_size * row_elems;
     int pidx = 0, poff = 0;   // page index and key offset of the next tile
-    int tcur = 0, tnx = 0;    // table entries of pages pidx and pidx + 1
+    int tcur = 0, tnx = 0;    // lane i: table entries of pages 64 (pidx / 64) + i and 64 further
     if constexpr (PAGED) {
-        tcur = __builtin_amdgcn_raw_buffer_load_b32(trs, 0, 0, 0);
-        tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, 4, 0, 0);
+        tcur = __builtin_amdgcn_raw_buffer_load_b32(trs, 4 * l, 0, 0);
+        tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, 4 * (64 + l), 0, 0);
     }
     const unsigned lds0 = lds_address(smem);
     // the next tile (they are loaded in order) into stage `stage`; bf16 V into vr
@@ -279,7 +282,11 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
             // the address comes from the table (page numbers clamped into the
             // pool), within it the address advances by one tile per load
             if (poff == 0) {
-                const int page = min(max(__builtin_amdgcn_readfirstlane(tcur), 0), a.num_pages - 1);
+                if (pidx > 0 && pidx % 64 == 0) {
+                    tcur = tnx;
+                    tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, 4 * (pidx + 64 + l), 0, 0);
+                }
+                const int page = min(max(__builtin_amdgcn_readlane(tcur, pidx % 64), 0), a.num_pages - 1);
                 const size_t t = (size_t)g * D + (size_t)page * page_elems;
                 ktile = reinterpret_cast<const S *>(a.k) + t;
                 vtile = reinterpret_cast<const S *>(a.v) + t;
@@ -308,10 +315,8 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
         if constexpr (PAGED) {
             poff += BC;
             const bool cross = poff == a.page_size;   // wave-uniform
-            tcur = cross ? tnx : tcur;
             poff = cross ? 0 : poff;
             pidx += cross ? 1 : 0;
-            tnx = __builtin_amdgcn_raw_buffer_load_b32(trs, (pidx + 1) * 4, 0, 0);
         }
     };
     // bf16 V of a loaded tile, as fp16, into its stage
