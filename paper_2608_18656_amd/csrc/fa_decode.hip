@@ -43,6 +43,7 @@ constexpr float TAU = 8.0f;    // lazy-rescale threshold (log2 units)
 constexpr int MIN_KEYS_PER_SPLIT = 256;
 constexpr int CUS = 256;                 // compute units
 constexpr long long LONG_SPLIT = 4096 * 100;   // keys (hundredths) beyond which one workgroup fills a CU's share of HBM
+constexpr int RANKED_KEYS = 512;         // keys per split from which an order by length pays
 constexpr int MAX_ROUNDS = 8;            // most rounds of one workgroup per CU that splitting may make
 
 struct DecodeArgs {
@@ -105,7 +106,9 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
     // Sequences of uneven length, in grids past one workgroup per CU: longest
     // first, so that the last round is short (64 x 32/8 heads, 512 to 4096 keys,
     // D = 128 119 -> 103 us; 40 of them, D = 64 39.4 -> 36.2); when all start at
-    // once, one workgroup for every CU, the others shortest first
+    // once, one workgroup for every CU, the others shortest first.  Ranking
+    // takes some 0.5 us: below 512 keys a split it is not done (13 x 32/8
+    // heads, 1050 keys, D = 64, 4 splits 11.7 us against 12.3 with it)
     if (a.ranked > 0) {
         const Lengths lens(a.seqlens, a.B, l);
         if (lens.uneven()) b = lens.nth_longest(b < a.ranked ? b : a.B - 1 - (b - a.ranked));
@@ -410,7 +413,7 @@ hipError_t launch_t(const Problem &p, int S, void *ws, hipStream_t stream) {
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.B = p.B;
     a.ranked = 0;
-    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > CUS) {
+    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > CUS && p.Nk >= RANKED_KEYS * (long long)S) {
         const long long per_seq = nblocks / p.B;
         a.ranked = nblocks <= resident(D) ? (int)((CUS + per_seq - 1) / per_seq) : p.B;
     }

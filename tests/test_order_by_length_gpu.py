@@ -44,8 +44,8 @@ def test_prefill_sequences_equal_their_own_calls(case):
             assert torch.equal(o[b:b + 1], ob) and torch.equal(lse[b:b + 1], lb), (b, lens[b])
 
 
-@pytest.mark.parametrize("case", [(40, 16, 16, 300, 64, "f16", 0), (64, 32, 8, 200, 128, "bf16", 0),
-                                  (12, 32, 8, 2048, 64, "bf16", 64), (65, 8, 8, 129, 128, "f16", 0)],
+@pytest.mark.parametrize("case", [(40, 16, 16, 640, 64, "f16", 64), (64, 32, 8, 520, 128, "bf16", 0),
+                                  (33, 8, 8, 1088, 64, "bf16", 0), (65, 8, 8, 600, 128, "f16", 0)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_decode(case):
     B, Hq, Hkv, Nk, D, dt, page = case
