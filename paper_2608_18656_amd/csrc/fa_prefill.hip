@@ -1,7 +1,8 @@
 // fa_prefill.hip -- prefill attention forward on gfx950 matrix cores.
 //
 // Work split.  A workgroup owns NS (query head, 32-row block) slots that read
-// the same key/value head: four (1, 2 and 8 exist for the packing ablation).
+// the same key/value head: four, or eight (1 and 2 exist for the packing
+// ablation).
 // When the group size G = Hq/Hkv allows, up to four of the slots
 // are query heads of one key/value group at the same rows -- the GPU form of
 // the inter-head packing of Sec. 4.1.1 and the GQA reuse of Sec. 4.1.2 (iv):
@@ -65,7 +66,7 @@ namespace fa {
 namespace {
 
 constexpr int WR = 32;        // query rows per slot
-constexpr int NSLOT = 4;      // slots per workgroup (the default; 1, 2 and 8 also exist)
+constexpr int NSLOT = 4;      // slots per workgroup where nothing speaks for another number
 constexpr float kMaxLaneSum = 4096.0f;   // largest 16-weight lane sum kept without a rescale
 
 struct PrefillArgs {
@@ -100,8 +101,9 @@ struct PrefillArgs {
 // from LDS in small groups to fit 168 VGPRs).  Three LDS stages (two for
 // one- and two-slot workgroups).
 // NS, the slots per workgroup (all reading one key/value head, each staged
-// tile serving all of them), is 4; 1, 2 and 8 exist for the packing ablation
-// (fewer slots stage more per thread, so they hold fewer waves per SIMD).
+// tile serving all of them), is 4, or 8 for some large grids (eight_slots); 1
+// and 2 exist for the packing ablation (fewer slots stage more per thread, so
+// they hold fewer waves per SIMD).
 template <int D, int NS = NSLOT> struct Cfg {
     static constexpr int NQ = D == 64 ? 2 : 1;       // waves per slot
     // waves per SIMD (what the registers allow; fewer slots stage more per thread)
@@ -637,6 +639,43 @@ int cu_count() {
     return n;
 }
 
+// Query heads per workgroup of `slots` slots: the most of one key/value group,
+// up to 4, that fill the slots evenly.
+int default_heads(int slots, int G) {
+    int hw = 1;
+    for (int c = 2; c <= (slots < 4 ? slots : 4); c *= 2)
+        if (slots % c == 0 && G % c == 0) hw = c;
+    return hw;
+}
+
+// Whether a D = 64 call takes eight slots per workgroup (one 16-wave workgroup
+// per CU) where the caller leaves the choice, rather than four (two of 8
+// waves).  Eight stage each tile half as often and run a full CU 4 to 5 %
+// faster; four end more evenly.  Non-causal calls, whose workgroups all take
+// the same time, compare rounds: a last round that leaves four-slot workgroups
+// alone on their CUs costs them 0.58 of a full one (4 against 8, us, 32/8
+// heads, bf16: 2048 rows 47.9 / 45.6; 2500 rows 77.8 / 92.9; 5920 rows 342.9 /
+// 329.6; 8192 rows 631 / 605; 16/1 heads, fp16, 16384 rows 1245 / 1198; 9000
+// rows, bf16 417.6 / 453.7).  Causal ones end on short workgroups in any case:
+// eight from four full rounds on, where four heads share a workgroup (32/8,
+// 8192 rows 329 / 320; 16/1, 16384 rows, fp16 628 / 621; but 6000 rows 185 /
+// 189, and 2 x 16/16 heads, 5000 rows 137 / 146).
+bool eight_slots(const Problem &p, bool causal) {
+    if (p.D != 64 || p.hw > 0 || p.seqlens || p.block_table) return false;
+    const long long cus = cu_count();
+    if (cus == 0) return false;
+    const int G = p.Hq / p.Hkv;
+    auto groups = [&](int slots) {
+        const int hw = default_heads(slots, G), rows = WR * slots / hw;
+        return ((long long)p.Nq + rows - 1) / rows * p.B * p.Hkv * (G / hw);
+    };
+    const long long four = groups(4), eight = groups(8);
+    if (causal) return G % 4 == 0 && four >= 8 * cus;
+    const long long rest = four % (2 * cus);
+    const long long cost4 = four / (2 * cus) * 1000 + (rest == 0 ? 0 : rest <= cus ? 580 : 1000);
+    return (eight + cus - 1) / cus * 955 < cost4;
+}
+
 template <typename TIN, typename TOUT, int D, int NS, bool CAUSAL>
 hipError_t launch_t(const Problem &p, hipStream_t stream) {
     using SM = Cfg<D, NS>;
@@ -653,12 +692,8 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.c = __builtin_fmaxf(__builtin_fabsf(p.scale), 1e-30f) * kLog2e;
     a.qsign = p.scale < 0.f ? 0x80008000u : 0u;
     const int G = p.Hq / p.Hkv;
-    // query heads per workgroup: the requested packing, else the most heads
-    // of one key/value group (up to 4) that fill the slots evenly
-    int hw = 1;
-    for (int c = 2; c <= (NS < 4 ? NS : 4); c *= 2)
-        if (NS % c == 0 && G % c == 0) hw = c;
-    a.HW = p.hw > 0 ? p.hw : hw;
+    // query heads per workgroup: the requested packing, else the default
+    a.HW = p.hw > 0 ? p.hw : default_heads(NS, G);
     const int RB = NS / a.HW;
     a.nmb = (p.Nq + WR * RB - 1) / (WR * RB);
     const long long nblocks = (long long)a.nmb * p.B * p.Hkv * (G / a.HW);
@@ -693,19 +728,15 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Slots per workgroup: four unless the caller asks for another layout.  With
-// the tiles staged without registers or LDS stores, eight slots per staged
-// tile save too little to make up for the coarser workgroups (D = 64, timed in
-// one process, four against eight: 32/4 heads, 5001 rows, fp16 131 against 142
-// us; 32/8 heads, 8192 rows, bf16 325 against 329; 16/1 heads, 16384 rows,
-// fp16 613 against 612, bf16 624 against 621).
 template <typename TIN, typename TOUT, int D, bool CAUSAL>
 hipError_t launch_s(const Problem &p, hipStream_t s) {
     switch (p.slots) {
     case 1: return launch_t<TIN, TOUT, D, 1, CAUSAL>(p, s);
     case 2: return launch_t<TIN, TOUT, D, 2, CAUSAL>(p, s);
+    case 4: return launch_t<TIN, TOUT, D, 4, CAUSAL>(p, s);
     case 8: return launch_t<TIN, TOUT, D, 8, CAUSAL>(p, s);
-    default: return launch_t<TIN, TOUT, D, NSLOT, CAUSAL>(p, s);
+    default:
+        return eight_slots(p, CAUSAL) ? launch_t<TIN, TOUT, D, 8, CAUSAL>(p, s) : launch_t<TIN, TOUT, D, NSLOT, CAUSAL>(p, s);
     }
 }
 
