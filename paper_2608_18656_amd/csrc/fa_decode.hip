@@ -231,8 +231,10 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
             }
         }
         float mx = max3(max3(s0[0], s0[1], s0[2]), max3(s0[3], s1[0], s1[1]), __builtin_fmaxf(s1[2], s1[3]));
-        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 16));
-        mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32));
+        // (by row swaps: an exchange through LDS would also wait for the chunk's
+        // other LDS reads; 32/4 heads, 1537 keys, D = 64 6.85 -> 6.66 us, 8 x 16/16,
+        // 1200 keys 12.84 -> 12.6, nothing where HBM bounds)
+        mx = pair_max(half_max(mx));
         const float m_tile = (mx == -INFINITY) ? -INFINITY : mx * a.c;
         const float m_new = __builtin_fmaxf(m_run, m_tile);
         const bool need = m_new > m_run + TAU;
@@ -271,8 +273,7 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
     }
 
     // ---- merge the waves' partial states through LDS
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = pair_sum(half_sum(l_run));
     __syncthreads();
     float *mf = reinterpret_cast<float *>(smem);     // [NW][QG][D + 2]
     float *mine = mf + (w * QG + lc) * (D + 2);

@@ -87,12 +87,6 @@ __device__ __forceinline__ float quad_max(float x) {
     auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return max_raw(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
-// Reductions over the lane pair (l, l ^ 16), as pair_sum over (l, l ^ 32).
-__device__ __forceinline__ float half_sum(float x) {
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // Element types as the kernel uses them: the storage scalar, and for fp16 /
 // bf16 the operand type of the matrix products.
 template <typename T> struct Elem;
