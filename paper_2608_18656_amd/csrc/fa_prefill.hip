@@ -674,7 +674,10 @@ int default_heads(int slots, int G) {
 // rows, bf16 417.6 / 453.7).  Causal ones end on short workgroups in any case:
 // eight from four full rounds on, where four heads share a workgroup (32/8,
 // 8192 rows 329 / 320; 16/1, 16384 rows, fp16 628 / 621; but 6000 rows 185 /
-// 189, and 2 x 16/16 heads, 5000 rows 137 / 146).
+// 189, and 2 x 16/16 heads, 5000 rows 137 / 146).  Lengths of their own are not
+// known here, and uneven ones want the finer workgroups (16 x 32/8 heads, 512
+// rows against up to 4096 keys 184 / 191, 8 of 1024 rows against 2048 111 / 124;
+// all equal 305 / 291).
 bool eight_slots(const Problem &p, bool causal) {
     if (p.D != 64 || p.hw > 0 || p.seqlens || p.block_table) return false;
     const long long cus = cu_count();
