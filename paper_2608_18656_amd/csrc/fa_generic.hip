@@ -36,7 +36,7 @@
 // 16 columns' maxima grow in turn, cost 50 more instructions.
 // Timed in turn, before (all fp32 MFMA, copies through registers with the
 // 16-bit values widened, a rescale whenever a maximum grows) and now, in us:
-// causal bf16 16/2 heads, 1111 rows, D = 96 39 -> 22; D = 256 205 -> 43;
+// causal bf16 16/2 heads, 1111 rows, D = 96 39 -> 21; D = 256 205 -> 43;
 // causal bf16 4 x 32/8, 2048 rows, D = 96 639 -> 223; decode bf16 16 x 32/8 x
 // 2048, D = 96 50 -> 25; causal fp32 16 heads, 777 rows, D = 64 27.5 -> 24.0,
 // D = 256 227 -> 82; fp32 2 heads, 128 rows, D = 64 7.7 -> 6.0.
@@ -533,7 +533,9 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
 //     D = 64 230 / 174
 //   16 bits, up to 128: (2, 4) against (4, 2): 16 x 512, D = 80 10.3 / 13.6;
 //     16/2 x 100 against 4000, D = 96 37 / 66; 32/8 x 2048 causal, D = 96
-//     95 / 63
+//     95 / 63; between them, causal calls of about square shape, (2, 2) against
+//     (4, 2): 16/2 x 1111, D = 96 23.1 / 24.7; 16 x 1400, D = 80 27.6 / 30.6 (not
+//     causal, 2 x 16/2 x 600, D = 88 27.4 / 21.8)
 //   fp32, above 128: (2, 2) against (4, 2): 16 x 777 causal, D = 192 63 / 88;
 //     16 x 1024, D = 192 152 / 118
 //   above 128, (4, 2) against (8, 1): bf16 16/2 x 1111 causal, D = 256
@@ -551,6 +553,12 @@ hipError_t launch_k(const Problem &p, hipStream_t s) {
         constexpr int FIT = 163840 / GCfg<TIN, DP, NS, KSP, NB>::BYTES;   // workgroups per CU by LDS
         const int rounds = p.causal && p.Nk < 2LL * p.Nq ? 2 : 1;
         if (groups(NS) <= CUS * (FIT < 2 ? FIT : 2) * rounds) return launch_t<TIN, TOUT, DP, NS, KSP, NB>(p, s);
+        if constexpr (!F32 && !WIDE) {   // (2, 2), where more of them than of (2, 4) start at once (96 columns)
+            constexpr int FIT2 = 163840 / GCfg<TIN, DP, 2, 2, NB>::BYTES;
+            if constexpr (FIT2 < 4 && FIT2 > 2 * FIT) {
+                if (rounds == 2 && groups(2) <= CUS * FIT2) return launch_t<TIN, TOUT, DP, 2, 2, NB>(p, s);
+            }
+        }
     }
     if constexpr (WIDE && !(F32 && DP == 160)) {
         if (groups(8) >= CUS) return launch_t<TIN, TOUT, DP, 8, 1, NB>(p, s);

@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (3, 180, 180, 17, 40, 24, False, "f16"),     # (4, 2)
     (1, 540, 270, 20, 70, 96, True, "bf16"),
+    (3, 180, 180, 30, 33, 88, True, "f16"),      # (2, 2): causal, about square
+    (1, 260, 260, 70, 70, 96, True, "bf16"),
     (2, 300, 300, 17, 40, 64, False, "f32"),     # (2, 4)
     (1, 33, 33, 250, 97, 192, False, "f32"),     # (4, 2)
     (1, 130, 130, 100, 37, 136, False, "f32"),
