@@ -68,24 +68,18 @@ __device__ __forceinline__ float4_t mfma4(float a, float b, float4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Maxima without the quieting of signalling NaNs that the compiler adds (the
-// operands are results of arithmetic).
-__device__ __forceinline__ float max3_raw(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-__device__ __forceinline__ float max_raw(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
+// Maxima that keep NaN, which the compiler forms without quieting its operands
+// first (with fmaxf, an instruction more for every score).  Not in assembly:
+// the compiler adds no wait states for what an assembly block reads, and these
+// read results of matrix instructions.
+__device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float max3_nan(float a, float b, float c) { return max_nan(max_nan(a, b), c); }
 // Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
 __device__ __forceinline__ float quad_max(float x) {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    x = max_nan(__uint_as_float(r[0]), __uint_as_float(r[1]));
     auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return max_raw(__uint_as_float(q[0]), __uint_as_float(q[1]));
+    return max_nan(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 // Element types as the kernel uses them: the storage scalar, and for fp16 /
 // bf16 the operand type of the matrix products.
@@ -120,20 +114,12 @@ __device__ __forceinline__ void split3(float p0, float p1, unsigned t[3], f16_t)
     const us2 some = __builtin_elementwise_min(
         __builtin_bit_cast(us2, __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u)), us2{1, 1});
     const half2_t h = __builtin_bit_cast(half2_t, __builtin_elementwise_max(__builtin_bit_cast(us2, cut(p0, p1)), some));
-    auto rest_lo = [](unsigned h, float x) {   // x - h[0]
-        float r;
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-        return r;
-    };
-    auto rest_hi = [](unsigned h, float x) {   // x - h[1]
-        float r;
-        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-        return r;
-    };
+    auto rest = [](_Float16 h, float x) { return __builtin_fmaf((float)h, -1.f, x); };   // x - h, one instruction
     t[0] = __builtin_bit_cast(unsigned, h);
-    const float m0 = rest_lo(t[0], p0), m1 = rest_hi(t[0], p1);
-    t[1] = __builtin_bit_cast(unsigned, cut(m0, m1));
-    t[2] = __builtin_bit_cast(unsigned, cut(rest_lo(t[1], m0), rest_hi(t[1], m1)));
+    const float m0 = rest(h[0], p0), m1 = rest(h[1], p1);
+    const half2_t g = cut(m0, m1);
+    t[1] = __builtin_bit_cast(unsigned, g);
+    t[2] = __builtin_bit_cast(unsigned, cut(rest(g[0], m0), rest(g[1], m1)));
 }
 
 constexpr int low_bit(int n, int cap) { return (n & -n) < cap ? (n & -n) : cap; }
@@ -355,10 +341,10 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a
         }
 
         // ---- streaming softmax
-        float mx = max3_raw(x[0], x[1], x[2]);
+        float mx = max3_nan(x[0], x[1], x[2]);
 #pragma unroll
-        for (int i = 3; i + 1 < 4 * NB; i += 2) mx = max3_raw(mx, x[i], x[i + 1]);
-        mx = quad_max(max_raw(mx, x[4 * NB - 1])) * a.c;
+        for (int i = 3; i + 1 < 4 * NB; i += 2) mx = max3_nan(mx, x[i], x[i + 1]);
+        mx = quad_max(max_nan(mx, x[4 * NB - 1])) * a.c;
         if (__builtin_amdgcn_ballot_w64(mx > lim)) {
             const bool over = mx > lim;
             const float b_new = over ? mx - HEADROOM : base;
