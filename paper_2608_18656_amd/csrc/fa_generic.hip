@@ -12,7 +12,9 @@
 //                 fp32 MFMA.  fp16 / bf16: the inputs' 16x16x32 MFMA with each
 //                 fp32 weight as the sum of three 16-bit terms, which holds all
 //                 its 24 bits; products are exact, sums fp32.  Three of those
-//                 take 48 cycles for 32 keys, eight fp32 ones 256.  V^T operands
+//                 take 48 cycles for 32 keys, eight fp32 ones 256.  (fp16 terms
+//                 hold a weight in full down to 2^-23 of the largest: 32 keys
+//                 with a smaller one are multiplied in fp32.)  V^T operands
 //                 by the transposing LDS read.
 //
 // Work split.  The Nq * G query rows of the G heads that read one key/value
@@ -74,6 +76,7 @@ __device__ __forceinline__ float4_t mfma4(float a, float b, float4_t c) {
 // read results of matrix instructions.
 __device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 __device__ __forceinline__ float max3_nan(float a, float b, float c) { return max_nan(max_nan(a, b), c); }
+__device__ __forceinline__ float min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 // Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
 __device__ __forceinline__ float quad_max(float x) {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -105,21 +108,19 @@ __device__ __forceinline__ void split3(float p0, float p1, unsigned t[3], bf16_t
     t[1] = top(m0, m1);
     t[2] = top(rest(t[1], lo, m0), rest(t[1], hi, m1));
 }
-// fp16 (weights up to 2^15): 11 bits at a time, exact down to a last place of
-// 2^-24, that is 2^-39 of the largest weight.  The first term of a weight
-// that is not zero is kept from being zero, so that an infinite value shows.
+// fp16 (weights up to 2^15): 11 bits at a time; t[1] and t[2] are kLowScale times
+// their terms, so that the last place is 2^-35 and a weight of kLeast or more
+// keeps all its bits.
+constexpr float kLowScale = 2048.f, kLeast = 0x1p-12f;
 __device__ __forceinline__ void split3(float p0, float p1, unsigned t[3], f16_t) {
-    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     auto cut = [](float a, float b) { return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(a, b)); };
-    const us2 some = __builtin_elementwise_min(
-        __builtin_bit_cast(us2, __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u)), us2{1, 1});
-    const half2_t h = __builtin_bit_cast(half2_t, __builtin_elementwise_max(__builtin_bit_cast(us2, cut(p0, p1)), some));
-    auto rest = [](_Float16 h, float x) { return __builtin_fmaf((float)h, -1.f, x); };   // x - h, one instruction
-    t[0] = __builtin_bit_cast(unsigned, h);
-    const float m0 = rest(h[0], p0), m1 = rest(h[1], p1);
+    const half2_t h = cut(p0, p1);
+    const float m0 = __builtin_fmaf((float)h[0], -kLowScale, kLowScale * p0);   // exact
+    const float m1 = __builtin_fmaf((float)h[1], -kLowScale, kLowScale * p1);
     const half2_t g = cut(m0, m1);
+    t[0] = __builtin_bit_cast(unsigned, h);
     t[1] = __builtin_bit_cast(unsigned, g);
-    t[2] = __builtin_bit_cast(unsigned, cut(rest(g[0], m0), rest(g[1], m1)));
+    t[2] = __builtin_bit_cast(unsigned, cut(m0 - (float)g[0], m1 - (float)g[1]));
 }
 
 constexpr int low_bit(int n, int cap) { return (n & -n) < cap ? (n & -n) : cap; }
@@ -149,11 +150,15 @@ template <typename TIN, int DP, int NSLOT, int KSP, int NB> struct GCfg {
     static __device__ __forceinline__ int vswz(int r) {
         return F32 ? ((r >> (2 - log2i(ZV))) & (ZV - 1)) << 2 : ((r >> (3 - log2i(ZV))) & (ZV - 1)) << 1;
     }
+    // waves per SIMD to keep registers for: one workgroup's, and two
+    // workgroups' where 128 registers are just enough for that (fp16 takes 133
+    // there otherwise)
+    static constexpr int WPE = !F32 && DP == 96 && NSLOT == 4 ? 4 : NW >= 4 ? NW / 4 : 1;
     static_assert(KBYTES % 1024 == 0 && (F32 || NB == 2), "tile shape");
 };
 
 template <typename TIN, typename TOUT, int DP, int NSLOT, int KSP, int NB>
-__global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a) {
+__global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_eu((GCfg<TIN, DP, NSLOT, KSP, NB>::WPE)))) void generic_kernel(GenericArgs a) {
     using SM = GCfg<TIN, DP, NSLOT, KSP, NB>;
     typedef typename Elem<TIN>::scalar S;
     constexpr bool F32 = SM::F32, F16 = __is_same(TIN, f16_t);
@@ -170,7 +175,8 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a
     constexpr int NSUM = !F32 ? 1 : DP <= 64 ? 2 : 4;
     // The base of a column's weights moves (and its sums are rescaled) only
     // when a score exceeds the largest one of that time by more than GROWTH;
-    // weights are at most 2^GROWTH, in fp16 2^15, for the range of their terms.
+    // weights are at most 2^GROWTH, in fp16 2^15 (the largest 2^11 or more), for
+    // the range of their terms.
     constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : 0.f;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SM::BYTES];
 
@@ -269,7 +275,7 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a
 
     // Accumulators.  16-bit inputs: the weights' first terms in oacc, the
     // others in olow (apart, so that an infinite value, times a zero term,
-    // does not turn into NaN).
+    // does not turn into NaN; in fp16 kLowScale times their sum).
     float4_t oacc[DT], olow[F32 ? 1 : DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
@@ -374,20 +380,45 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
         } else {
             typedef typename TIN::vec8 V8;
-            uint4_t pt[3];
+            // fp16: does some weight lie below what three terms hold in full?
+            unsigned long long small = 0;
+            if constexpr (F16) {
+                float least = p[0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                unsigned t[3];
-                split3(p[2 * i], p[2 * i + 1], t, TIN());
+                for (int i = 1; i < 8; ++i) least = min_nan(least, p[i]);
+                if (__builtin_amdgcn_ballot_w64(least < kLeast) != 0) {
+                    bool some = false;
 #pragma unroll
-                for (int n = 0; n < 3; ++n) pt[n][i] = t[n];
+                    for (int i = 0; i < 8; ++i) some |= p[i] > 0.f && p[i] < kLeast;
+                    small = __builtin_amdgcn_ballot_w64(some);
+                }
+                if (small) {   // the products in fp32: element i of a lane's operand is the value of its weight i
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) {
+                        const V8 vv = as_vec8<V8>(VPRE ? va[0][dt] : vread(0, dt));
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) oacc[dt] = mfma4((float)vv[i], p[i], oacc[dt]);
+                        __builtin_amdgcn_sched_barrier(0);   // one tile's operands at a time, in few registers
+                    }
+                }
+                asm volatile("" : "+s"(small));   // two conditions: as the sides of one, each has its own registers
             }
+            if (!small) {
+                uint4_t pt[3];
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const V8 vv = as_vec8<V8>(VPRE ? va[0][dt] : vread(0, dt));
-                oacc[dt] = mfma16(vv, as_vec8<V8>(pt[0]), oacc[dt]);
-                olow[dt] = mfma16(vv, as_vec8<V8>(pt[1]), olow[dt]);
-                olow[dt] = mfma16(vv, as_vec8<V8>(pt[2]), olow[dt]);
+                for (int i = 0; i < 4; ++i) {
+                    unsigned t[3];
+                    split3(p[2 * i], p[2 * i + 1], t, TIN());
+#pragma unroll
+                    for (int n = 0; n < 3; ++n) pt[n][i] = t[n];
+                }
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const V8 vv = as_vec8<V8>(VPRE ? va[0][dt] : vread(0, dt));
+                    oacc[dt] = mfma16(vv, as_vec8<V8>(pt[0]), oacc[dt]);
+                    olow[dt] = mfma16(vv, as_vec8<V8>(pt[1]), olow[dt]);
+                    olow[dt] = mfma16(vv, as_vec8<V8>(pt[2]), olow[dt]);
+                }
             }
         }
     };
@@ -409,7 +440,8 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) void generic_kernel(GenericArgs a
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int r = 0; r < 4; ++r)   // (the first terms' sum alone where it is not finite)
-                oacc[dt][r] = oacc[dt][r] - oacc[dt][r] == 0.f ? oacc[dt][r] + olow[dt][r] : oacc[dt][r];
+                oacc[dt][r] = oacc[dt][r] - oacc[dt][r] == 0.f
+                                  ? __builtin_fmaf(olow[dt][r], F16 ? 1.f / kLowScale : 1.f, oacc[dt][r]) : oacc[dt][r];
     }
 
     // ---- merge the key parts of each slot through LDS

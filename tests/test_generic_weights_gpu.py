@@ -36,3 +36,25 @@ def test_scores_from_the_last_columns(D, dtype):
     k[..., -4:] = torch.randint(-7, 8, (1, 300, 4, 1), generator=gen).float()
     v = torch.randn(1, 300, 4, D, generator=gen)
     _against_oracle(*(t.to(DTS[dtype]) for t in (q, k, v)), 1.0)
+
+
+@pytest.mark.parametrize("D,dtype", [(96, "f16"), (160, "f16"), (96, "bf16"), (64, "f32")])
+@pytest.mark.parametrize("gap", [0.5, 8.5, 14.0, 17.0, 20.75, 24.25, 30.0, 40.0])
+def test_values_on_keys_of_small_weight(D, dtype, gap):
+    """One key outweighs the 1023 others by e^gap and has the value 0; the others'
+    large values make up the result, so that their weights' own accuracy shows:
+    at most 1024 products and as many additions, each within 2^-24, in each of
+    the two sums that a result is the quotient of (2.5e-4 in the worst case; a
+    weight of 16 bits is off by 2^-11 or more).  Every other row weighs all keys
+    the same."""
+    gen = torch.Generator().manual_seed(5)
+    q, k = torch.zeros(1, 21, 2, D), torch.zeros(1, 1024, 2, D)
+    q[:, ::2, :, 0] = 1.0
+    k[0, 37, :, 0] = gap
+    v = 3e4 + 3e4 * torch.rand(1, 1024, 2, D, generator=gen)
+    v[0, 37] = 0.0
+    q, k, v = (t.to(DTS[dtype]) for t in (q, k, v))
+    o, lse = fa.fwd(q.cuda(), k.cuda(), v.cuda(), causal=False, scale=1.0, out_dtype=torch.float32)
+    o_ref, l_ref = oracle.attention(q, k, v, False, 1.0)
+    assert (np.abs(to_np(o) - o_ref) <= 2.5e-4 * np.abs(o_ref)).all()
+    assert np.abs(to_np(lse) - l_ref).max() <= 1e-4
