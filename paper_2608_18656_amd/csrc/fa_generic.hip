@@ -174,10 +174,10 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
     // of 64 steps would round more than the scores of sharp softmaxes allow
     constexpr int NSUM = !F32 ? 1 : DP <= 64 ? 2 : 4;
     // The base of a column's weights moves (and its sums are rescaled) only
-    // when a score exceeds the largest one of that time by more than GROWTH;
-    // weights are at most 2^GROWTH, in fp16 2^15 (the largest 2^11 or more), for
-    // the range of their terms.
-    constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : 0.f;
+    // when a score exceeds the largest one of that time by more than GROWTH.
+    // That one then weighs 2^HEADROOM, so weights are at most 1 (a weight times
+    // any value stays in range), in fp16 2^15, for the range of their terms.
+    constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : -GROWTH;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SM::BYTES];
 
     const int tid = threadIdx.x, l = tid & 63;

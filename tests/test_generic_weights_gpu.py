@@ -58,3 +58,18 @@ def test_values_on_keys_of_small_weight(D, dtype, gap):
     o_ref, l_ref = oracle.attention(q, k, v, False, 1.0)
     assert (np.abs(to_np(o) - o_ref) <= 2.5e-4 * np.abs(o_ref)).all()
     assert np.abs(to_np(lse) - l_ref).max() <= 1e-4
+
+
+@pytest.mark.parametrize("D,dtype", [(96, "bf16"), (160, "bf16"), (64, "f32"), (192, "f32")])
+@pytest.mark.parametrize("heavy", [2.625, 5.5])
+def test_values_near_the_end_of_the_range(D, dtype, heavy):
+    """The largest weight, seen late, belongs to a value of 2^126: weights above 1
+    would take the product out of range."""
+    q, k, v = (torch.zeros(1, n, 2, D) for n in (21, 300, 300))
+    q[..., 0] = 1.0
+    k[0, 290, :, 0] = heavy
+    v[0, 290] = 2.0 ** 126
+    q, k, v = (t.to(DTS[dtype]) for t in (q, k, v))
+    o, _ = fa.fwd(q.cuda(), k.cuda(), v.cuda(), causal=False, scale=1.0, out_dtype=torch.float32)
+    o_ref, _ = oracle.attention(q, k, v, False, 1.0)
+    assert (np.abs(to_np(o) - o_ref) <= 2e-5 * o_ref).all()   # 300 additions within 2^-24 each
