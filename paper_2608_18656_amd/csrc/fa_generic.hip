@@ -59,7 +59,7 @@ struct GenericArgs {
     float *lse;
     int B, Hq, Hkv, Nq, Nk, D;
     int causal;
-    float c;          // max(|scale|, tiny) * log2(e), > 0
+    float c;          // |scale| * log2(e), > 0
     unsigned qsign;   // sign bits of an element word, to negate q (scale < 0), else 0
     int nvb;   // blocks of 16 NSLOT columns per key/value head
     Divisor per_vb, nkv, group;   // B * Hkv, Hkv, Hq / Hkv
@@ -524,8 +524,9 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.B = p.B; a.Hq = p.Hq; a.Hkv = p.Hkv; a.Nq = p.Nq; a.Nk = p.Nk; a.D = p.D;
     a.causal = p.causal;
     a.seqlens = p.seqlens;
-    // A zero scale keeps a tiny positive factor, for masked scores of -inf.
-    a.c = __builtin_fmaxf(__builtin_fabsf(p.scale), 1e-30f) * kLog2e;
+    // A zero scale keeps a positive factor, for masked scores of -inf: the least
+    // there is, which moves no weight by more than 2^-21.
+    a.c = __builtin_fmaxf(__builtin_fabsf(p.scale) * kLog2e, 0x1p-149f);
     a.qsign = p.scale < 0.f ? (sizeof(typename Elem<TIN>::scalar) == 4 ? 0x80000000u : 0x80008000u) : 0u;
     constexpr int COLS = QB * NSLOT;
     const long long nvb = ((long long)p.Nq * (p.Hq / p.Hkv) + COLS - 1) / COLS;

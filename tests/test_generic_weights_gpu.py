@@ -73,3 +73,14 @@ def test_values_near_the_end_of_the_range(D, dtype, heavy):
     o, _ = fa.fwd(q.cuda(), k.cuda(), v.cuda(), causal=False, scale=1.0, out_dtype=torch.float32)
     o_ref, _ = oracle.attention(q, k, v, False, 1.0)
     assert (np.abs(to_np(o) - o_ref) <= 2e-5 * o_ref).all()   # 300 additions within 2^-24 each
+
+
+@pytest.mark.parametrize("D,dtype", [(64, "f32"), (192, "f32"), (96, "bf16"), (256, "bf16")])
+@pytest.mark.parametrize("scale", [0.0, 1e-33, -2e-33])
+def test_large_scores_of_a_tiny_scale(D, dtype, scale):
+    """Products of q and k of up to some 10^34: a scale of 0 weighs all keys the
+    same, one of 10^-33 leaves ordinary scores."""
+    gen = torch.Generator().manual_seed(8)
+    q, k, v = (torch.randn(1, n, 2, D, generator=gen) for n in (21, 150, 150))
+    q, k, v = (t.to(DTS[dtype]) for t in (q * 1e16, k * 3e16 / D ** 0.5, v))
+    _against_oracle(q, k, v, scale, causal=True)
