@@ -125,7 +125,8 @@ fa_status_t fa_fwd(const void *q, const void *k, const void *v, void *o, float *
                    void *stream, fa_dtype_t in_dtype, fa_dtype_t out_dtype);
 
 /* Decode path with an explicit split count (Nq == 1 and fp16 / bf16 with
- * D in {64, 128} only; otherwise behaves like fa_fwd).  num_splits = 0 picks
+ * D in {64, 128} only, and 32 key rows of Hkv * D elements below 2 GiB;
+ * otherwise behaves like fa_fwd).  num_splits = 0 picks
  * the count fa_fwd would use; 1..FA_MAX_SPLITS forces it (splits left
  * without keys are allowed and contribute nothing to the merge). */
 fa_status_t fa_fwd_splitkv(const void *q, const void *k, const void *v, void *o, float *lse,

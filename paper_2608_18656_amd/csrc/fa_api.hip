@@ -142,7 +142,7 @@ fa_status_t run(const void *q, const void *k, const void *v, void *o, float *lse
                   pg.block_table, pg.page_size, pg.max_pages, pg.num_pages};
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e;
-    if (fa::decode_supported(Nq, D, in)) {
+    if (fa::decode_supported(Nq, Hkv, D, in)) {
         const int S = splits_req > 0 ? splits_req : fa::decode_default_splits(B, Hq, Hkv, Nk, D);
         const size_t need = fa::decode_workspace_bytes(B, Hq, D, S);
         void *ws = nullptr;
@@ -166,7 +166,7 @@ fa_status_t run(const void *q, const void *k, const void *v, void *o, float *lse
                 return FA_ERR_ALIAS;
         }
         e = fa::launch_decode(p, S, ws, s);
-    } else if (fa::prefill_supported(D, in)) {
+    } else if (fa::prefill_supported(Hkv, D, in)) {
         e = fa::launch_prefill(p, s);
     } else {
         e = fa::launch_generic(p, s);
@@ -283,7 +283,7 @@ fa_status_t kvcache_paged(const void *q, const void *k_pages, const void *v_page
     if ((reinterpret_cast<uintptr_t>(seqlens_k) & 3) || (reinterpret_cast<uintptr_t>(block_table) & 3))
         return FA_ERR_ALIGN;
     const int Nk = page_size * max_pages;
-    // only the matrix-core kernels read pages
+    // fp16 / bf16 with D of 64 or 128 only
     if (in_dtype != FA_F16 && in_dtype != FA_BF16) {
         const fa_status_t st = validate_core(q, k_pages, v_pages, o, lse, B, Hq, Hkv, Nq, Nk, D, causal,
                                              scale, in_dtype, out_dtype, (long long)num_pages * page_size);
@@ -361,7 +361,7 @@ fa_status_t fa_fwd_splitkv_noalloc(const void *q, const void *k, const void *v, 
     if (st != FA_OK) return st;
     if (num_splits < 0 || num_splits > FA_MAX_SPLITS) return FA_ERR_SPLITS;
     CallWs cws{nullptr, 0};
-    if (fa::decode_supported(Nq, D, in_dtype)) {
+    if (fa::decode_supported(Nq, Hkv, D, in_dtype)) {
         const int S = num_splits > 0 ? num_splits : fa::decode_default_splits(B, Hq, Hkv, Nk, D);
         if (fa::decode_workspace_bytes(B, Hq, D, S) > kScratchBytes) return FA_ERR_WORKSPACE;
         st = scratch_address(&cws.ptr);
@@ -396,7 +396,7 @@ fa_status_t fa_fwd_kvcache_paged_ws(const void *q, const void *k_pages, const vo
 size_t fa_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, fa_dtype_t in_dtype,
                           int num_splits) {
     if (B < 1 || Hq < 1 || Hkv < 1 || Nk < 1 || Hq % Hkv != 0) return 0;
-    if (!fa::decode_supported(Nq, D, in_dtype)) return 0;
+    if (!fa::decode_supported(Nq, Hkv, D, in_dtype)) return 0;
     if (num_splits < 0 || num_splits > FA_MAX_SPLITS) return 0;
     const int S = num_splits > 0 ? num_splits : fa::decode_default_splits(B, Hq, Hkv, Nk, D);
     return fa::decode_workspace_bytes(B, Hq, D, S);

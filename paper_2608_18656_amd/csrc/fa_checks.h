@@ -27,6 +27,13 @@ inline bool mul_ok(long long a, long long b, long long *r) {
     return true;
 }
 
+// Whether the offsets within a tile of `rows` key rows of 16-bit elements fit
+// the 31 bits that the prefill and decode kernels have for them: key rows of
+// some 33 MiB (64 rows) or 66 MiB (32 rows) and more do not.
+inline bool tile_fits(int Hkv, int D, int rows) {
+    return (long long)(rows - 1) * Hkv * D * 2 + 2 * D <= 0x7fffffffLL;
+}
+
 // The argument checks of every attention entry point.  kv_rows: rows of
 // Hkv * D elements that k and v each hold (-1: B * Nk, the contiguous layout).
 inline fa_status_t validate_core(const void *q, const void *k, const void *v, const void *o,

@@ -30,6 +30,7 @@
 // small ones the chain launch, lengths, keys, merge, second launch (7 us for
 // 32/4 heads, 1537 keys, D = 64).  Loads two chunks ahead (144 and 244
 // registers) and 16-wave workgroups at D = 64 gained nothing.
+#include "fa_checks.h"
 #include "fa_common.h"
 #include "fa_internal.h"
 
@@ -438,8 +439,8 @@ hipError_t launch_d(const Problem &p, int S, void *ws, hipStream_t s) {
 
 }  // namespace
 
-bool decode_supported(int Nq, int D, fa_dtype_t in) {
-    return Nq == 1 && (D == 64 || D == 128) && (in == FA_F16 || in == FA_BF16);
+bool decode_supported(int Nq, int Hkv, int D, fa_dtype_t in) {
+    return Nq == 1 && (D == 64 || D == 128) && (in == FA_F16 || in == FA_BF16) && tile_fits(Hkv, D, KPW);
 }
 
 // Split count.  A call has U (batch, key/value head, query group) units and

@@ -1,7 +1,7 @@
 // fa_generic.hip -- attention forward with fp32 weights, for the cases the
-// half-precision matrix kernels do not take: fp32 inputs, and fp16 / bf16 with
+// half-precision matrix kernels do not take: fp32 inputs, fp16 / bf16 with
 // a head dimension other than 64 or 128 (any D with D % 8 == 0 and D <= 256),
-// prefill and decode.
+// and key rows too long for those kernels' offsets (tile_fits), prefill and decode.
 //
 // Scores are fp32 sums; weights, their sums and the accumulators are fp32.
 // Both products run on the matrix cores:
@@ -64,6 +64,9 @@ struct GenericArgs {
     int nvb;   // blocks of 16 NSLOT columns per key/value head
     Divisor per_vb, nkv, group;   // B * Hkv, Hkv, Hq / Hkv
     const int *seqlens;   // valid keys per batch element (NULL: Nk for all)
+    const int *block_table;   // paged K/V: page of each key block (see Problem)
+    Divisor page_size;
+    int max_pages, num_pages;
 };
 
 __device__ __forceinline__ float4_t mfma4(float a, float b, float4_t c) {
@@ -164,6 +167,7 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
     constexpr bool F32 = SM::F32, F16 = __is_same(TIN, f16_t);
     constexpr int ES = SM::ES, E = SM::E, CPR = SM::CPR, KB = SM::KB, BC = SM::BC, NW = SM::NW, NP = SM::NP;
     constexpr int DT = DP / 16;                  // 16-column tiles of O
+    constexpr bool PAGES = !F32 && (DP == 64 || DP == 128);   // K/V may come in pages
     constexpr bool VPRE = DP <= 128;             // value operands are read ahead of the softmax
     // fp32 products are issued at raised wave priority up to 64 columns: the
     // SIMD's other waves then fill the gaps with vector work (causal 16 heads,
@@ -230,7 +234,9 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
     // 64 j .. 64 j + 63, lane l's the l-th; chunks past D and keys past the
     // end (past the view's) become zeros.
     const long long pitch = (long long)a.Hkv * D * ES;   // bytes between consecutive keys
-    const bool far = pitch * BC > 0x7fffffffLL;          // a tile's offsets exceed a buffer view's 31 bits
+    // a tile's offsets exceed a buffer view's 31 bits; so they do where K/V
+    // come in pages (other paged calls take the prefill and decode kernels)
+    const bool far = pitch * BC > 0x7fffffffLL;
     int koff[NP], voff[NP];
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
         voff[j] = E * cv < D ? r * (int)pitch + 16 * cv : (int)0x80000000;
     }
     const unsigned lds0 = lds_address(smem);
-    const size_t head0 = ((size_t)b * a.Nk * a.Hkv + g) * (size_t)D * ES;
+    const size_t head0 = ((PAGES && a.block_table ? 0 : (size_t)b * a.Nk * a.Hkv) + g) * (size_t)D * ES;
     const char *ktile = reinterpret_cast<const char *>(a.k) + head0;
     const char *vtile = reinterpret_cast<const char *>(a.v) + head0;
     long long left = (long long)(Nk - 1) * pitch + D * ES;   // bytes from the next tile's first key to the last one's end
@@ -255,21 +261,29 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
             for (int j = 0; j < NP; ++j)
                 if (SM::PIECES % NW == 0 || w + NW * j < SM::PIECES)
                     load_lds16(vtile, nrec, dst + SM::KBYTES + 1024 * NW * j, voff[j]);
-        } else {   // the same through registers, with 64-bit offsets
+        } else {   // the same through registers, with 64-bit offsets, a page number for each row of paged K/V
             for (int e = tid; e < BC * CPR; e += 64 * NW) {
                 const int r = e / CPR, c = e % CPR;
                 uint4_t kc = uint4_t{0u, 0u, 0u, 0u}, vc = kc;
                 if (k0 + r < Nk && E * c < D) {
-                    kc = ld16(ktile + r * pitch + 16 * c);
-                    vc = ld16(vtile + r * pitch + 16 * c);
+                    long long row = r;   // from the tile's first key, or from the pool's first row
+                    if (PAGES && a.block_table) {
+                        const int pi = (int)a.page_size.div(k0 + r);
+                        const int page = min(max(a.block_table[(size_t)b * a.max_pages + pi], 0), a.num_pages - 1);
+                        row = (long long)page * a.page_size.d + (k0 + r - pi * (int)a.page_size.d);
+                    }
+                    kc = ld16(ktile + row * pitch + 16 * c);
+                    vc = ld16(vtile + row * pitch + 16 * c);
                 }
                 unsigned char *row_at = smem + st * SM::STAGE + r * (DP * ES);
                 st16(row_at + 16 * (c ^ SM::kswz(r)), kc);
                 st16(row_at + SM::KBYTES + 16 * (c ^ SM::vswz(r)), vc);
             }
         }
-        ktile += BC * pitch;
-        vtile += BC * pitch;
+        if (!PAGES || !a.block_table) {
+            ktile += BC * pitch;
+            vtile += BC * pitch;
+        }
         left -= BC * pitch;
     };
 
@@ -524,6 +538,10 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.B = p.B; a.Hq = p.Hq; a.Hkv = p.Hkv; a.Nq = p.Nq; a.Nk = p.Nk; a.D = p.D;
     a.causal = p.causal;
     a.seqlens = p.seqlens;
+    a.block_table = p.block_table;
+    a.page_size = Divisor(p.block_table ? p.page_size : 1);
+    a.max_pages = p.max_pages;
+    a.num_pages = p.num_pages;
     // A zero scale keeps a positive factor, for masked scores of -inf: the least
     // there is, which moves no weight by more than 2^-21.
     a.c = __builtin_fmaxf(__builtin_fabsf(p.scale) * kLog2e, 0x1p-149f);

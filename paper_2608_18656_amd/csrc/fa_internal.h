@@ -37,8 +37,8 @@ hipError_t launch_q8_gemv(const void *w, const void *x, void *y, int M, int K, f
                           fa_dtype_t y_dtype, hipStream_t stream);
 
 // Decode split planning (shared by the dispatcher and fa_workspace_bytes).
-bool decode_supported(int Nq, int D, fa_dtype_t in);
-bool prefill_supported(int D, fa_dtype_t in);
+bool decode_supported(int Nq, int Hkv, int D, fa_dtype_t in);
+bool prefill_supported(int Hkv, int D, fa_dtype_t in);
 int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D);
 size_t decode_workspace_bytes(int B, int Hq, int D, int splits);
 

@@ -59,6 +59,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "fa_checks.h"
 #include "fa_common.h"
 #include "fa_internal.h"
 
@@ -247,7 +248,7 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // in K and V, which advances by one tile per load, and its number.  The
     // buffer view of a tile ends after its last valid key (keys past it read
     // as zero): a full tile's extent for the first Nk / BC tiles, then that of
-    // the remaining keys, if any (one tile's extent fits 31 bits).
+    // the remaining keys, if any (one tile's extent fits 31 bits: tile_fits).
     const size_t head0 = ((size_t)b * a.Nk * a.Hkv + g) * D;
     const S *ktile = reinterpret_cast<const S *>(a.k) + (PAGED ? 0 : head0);
     const S *vtile = reinterpret_cast<const S *>(a.v) + (PAGED ? 0 : head0);
@@ -767,8 +768,8 @@ hipError_t launch_d(const Problem &p, hipStream_t s) {
 
 }  // namespace
 
-bool prefill_supported(int D, fa_dtype_t in) {
-    return (D == 64 || D == 128) && (in == FA_F16 || in == FA_BF16);
+bool prefill_supported(int Hkv, int D, fa_dtype_t in) {
+    return (D == 64 || D == 128) && (in == FA_F16 || in == FA_BF16) && tile_fits(Hkv, D, D == 64 ? Cfg<64>::BC : Cfg<128>::BC);
 }
 
 hipError_t launch_prefill(const Problem &p, hipStream_t stream) {
