@@ -221,7 +221,8 @@ fa_status_t fa_fwd_kvcache_paged(const void *q, const void *k_pages, const void 
                                  fa_dtype_t in_dtype, fa_dtype_t out_dtype);
 
 /* Bytes of decode workspace a call with these sizes needs (0 when the call
- * takes no split-KV path).  num_splits as in fa_fwd_splitkv. */
+ * takes no split-KV path).  num_splits as in fa_fwd_splitkv; with 0 the size
+ * serves every call with a shorter cache (Nk) as well. */
 size_t fa_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, fa_dtype_t in_dtype,
                           int num_splits);
 

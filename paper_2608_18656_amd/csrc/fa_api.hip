@@ -43,7 +43,8 @@ std::vector<OwnedWs> g_owned;
 std::vector<Retired> g_retired;
 std::mutex g_ws_mu;
 
-fa_status_t get_workspace(size_t need, hipStream_t stream, void **out, bool *user) {
+// need: what the call uses; room: what a new buffer holds (for shorter caches too).
+fa_status_t get_workspace(size_t need, size_t room, hipStream_t stream, void **out, bool *user) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return FA_ERR_HIP;
     std::lock_guard<std::mutex> lk(g_ws_mu);
@@ -68,7 +69,7 @@ fa_status_t get_workspace(size_t need, hipStream_t stream, void **out, bool *use
         return FA_ERR_WORKSPACE;
     }
     if (cs != hipStreamCaptureStatusNone) return FA_ERR_WORKSPACE;
-    const size_t sz = need < ((size_t)1 << 20) ? ((size_t)1 << 20) : need;
+    const size_t sz = room < ((size_t)1 << 20) ? ((size_t)1 << 20) : room;
     void *ptr = nullptr;
     if (hipMalloc(&ptr, sz) != hipSuccess) {
         (void)hipGetLastError();
@@ -154,7 +155,8 @@ fa_status_t run(const void *q, const void *k, const void *v, void *o, float *lse
             ws = cws->ptr;
             user = true;
         } else {
-            st = get_workspace(need, s, &ws, &user);
+            const int most = splits_req > 0 ? splits_req : fa::decode_most_splits(B, Hq, Hkv, Nk, D);
+            st = get_workspace(need, fa::decode_workspace_bytes(B, Hq, D, most), s, &ws, &user);
             if (st != FA_OK) return st;
         }
         if (user) {   // a caller-owned workspace must not overlap the call's tensors
@@ -398,7 +400,8 @@ size_t fa_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int D, fa_dtyp
     if (B < 1 || Hq < 1 || Hkv < 1 || Nk < 1 || Hq % Hkv != 0) return 0;
     if (!fa::decode_supported(Nq, Hkv, D, in_dtype)) return 0;
     if (num_splits < 0 || num_splits > FA_MAX_SPLITS) return 0;
-    const int S = num_splits > 0 ? num_splits : fa::decode_default_splits(B, Hq, Hkv, Nk, D);
+    // enough for every shorter cache as well: a program sizes its workspace once
+    const int S = num_splits > 0 ? num_splits : fa::decode_most_splits(B, Hq, Hkv, Nk, D);
     return fa::decode_workspace_bytes(B, Hq, D, S);
 }
 

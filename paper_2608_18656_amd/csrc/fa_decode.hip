@@ -482,6 +482,20 @@ int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D) {
     return (int)best;
 }
 
+// The most splits of any cache of up to Nk keys.  The count grows with the cache
+// (a candidate of more splits has the larger constant part, so one that is
+// cheaper at some length stays so), but for the 50 % of long splits: where
+// they can apply, the largest candidate.
+int decode_most_splits(int B, int Hq, int Hkv, int Nk, int D) {
+    if (resident(D) == CUS || Nk <= LONG_SPLIT / 100) return decode_default_splits(B, Hq, Hkv, Nk, D);
+    const long long units = (long long)B * Hkv * ((Hq / Hkv + QG - 1) / QG);
+    const long long cap = (Nk + (long long)MIN_KEYS_PER_SPLIT - 1) / MIN_KEYS_PER_SPLIT;
+    long long S = MAX_ROUNDS * (long long)CUS / units;
+    if (S > cap) S = cap;
+    if (S > FA_MAX_SPLITS) S = FA_MAX_SPLITS;
+    return S < 1 ? 1 : (int)S;
+}
+
 size_t decode_workspace_bytes(int B, int Hq, int D, int splits) {
     return (size_t)B * Hq * splits * (size_t)(D + 2) * sizeof(float);
 }

@@ -40,6 +40,7 @@ hipError_t launch_q8_gemv(const void *w, const void *x, void *y, int M, int K, f
 bool decode_supported(int Nq, int Hkv, int D, fa_dtype_t in);
 bool prefill_supported(int Hkv, int D, fa_dtype_t in);
 int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D);
+int decode_most_splits(int B, int Hq, int Hkv, int Nk, int D);   // of any cache of up to Nk keys
 size_t decode_workspace_bytes(int B, int Hq, int D, int splits);
 
 // Unfused path: supported shapes and the workspace it needs (0 when a size is
