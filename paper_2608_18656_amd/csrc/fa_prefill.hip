@@ -667,20 +667,27 @@ int default_heads(int slots, int G) {
 // Whether a D = 64 call takes eight slots per workgroup (one 16-wave workgroup
 // per CU) where the caller leaves the choice, rather than four (two of 8
 // waves).  Eight stage each tile half as often and run a full CU 4 to 5 %
-// faster; four end more evenly.  Non-causal calls, whose workgroups all take
-// the same time, compare rounds: a last round that leaves four-slot workgroups
-// alone on their CUs costs them 0.58 of a full one (4 against 8, us, 32/8
-// heads, bf16: 2048 rows 47.9 / 45.6; 2500 rows 77.8 / 92.9; 5920 rows 342.9 /
-// 329.6; 8192 rows 631 / 605; 16/1 heads, fp16, 16384 rows 1245 / 1198; 9000
-// rows, bf16 417.6 / 453.7).  Causal ones end on short workgroups in any case:
-// eight from four full rounds on, where four heads share a workgroup (32/8,
-// 8192 rows 329 / 320; 16/1, 16384 rows, fp16 628 / 621; but 6000 rows 185 /
-// 189, and 2 x 16/16 heads, 5000 rows 137 / 146).  Lengths of their own are not
-// known here, and uneven ones want the finer workgroups (16 x 32/8 heads, 512
-// rows against up to 4096 keys 184 / 191, 8 of 1024 rows against 2048 111 / 124;
-// all equal 305 / 291).
+// faster; four end more evenly.  Calls whose workgroups all take about the same
+// time, not causal or few rows against many keys, compare rounds: a last round
+// that leaves four-slot workgroups alone on their CUs costs them 0.58 of a full
+// one (4 against 8, us, 32/8 heads, bf16: 1056 rows 24.8 / 23.3; 1400 rows
+// 28.9 / 26.9; 2048 rows 47.9 / 45.6; 2500 rows 77.8 / 92.9; 5920 rows 342.9 /
+// 329.6; 8192 rows 631 / 605; 16/1 heads, 3000 rows 54.0 / 48.1; fp16, 16384 rows
+// 1245 / 1198; bf16, 9000 rows 417.6 / 453.7; causal, 4 x 1024 rows against 4096
+// keys 141.7 / 134.2, 5 x 1000 against 5000 216 / 228).  Square causal calls
+// end on short workgroups in any case: eight from four full rounds on, where
+// four heads share a workgroup (32/8, 8192 rows 329 / 320; 16/1, 16384 rows,
+// fp16 628 / 621; but 6000 rows 185 / 189, and 2 x 16/16 heads, 5000 rows 137 /
+// 146).  Lengths of their own are not known here.  Where they are equal, eight
+// gain as much (16 x 32/8 heads, 512 rows against 4096 keys 370 / 348; 32 x 16/2,
+// 256 rows 205 / 184), and long uneven ones lose at most 1 % (the first call
+// with 614 keys and more 180 / 181); short ones would lose up to 12 % (16 x 512
+// rows against up to 1024 keys 64.5 / 72.5, against 2048 99.8 / 104.1, where
+// equal ones gain 1.4 %), and so would those of one round, whose long and short
+// workgroups then no longer share CUs (4 x 512 rows against 2048 to 4096 keys
+// 62.7 / 69.2): eight from 2048 keys and two rounds on.
 bool eight_slots(const Problem &p, bool causal) {
-    if (p.D != 64 || p.hw > 0 || p.seqlens || p.block_table) return false;
+    if (p.D != 64 || p.hw > 0 || p.block_table || (p.seqlens && p.Nk < 2048)) return false;
     const long long cus = cu_count();
     if (cus == 0) return false;
     const int G = p.Hq / p.Hkv;
@@ -689,7 +696,8 @@ bool eight_slots(const Problem &p, bool causal) {
         return ((long long)p.Nq + rows - 1) / rows * p.B * p.Hkv * (G / hw);
     };
     const long long four = groups(4), eight = groups(8);
-    if (causal) return G % 4 == 0 && four >= 8 * cus;
+    if (p.seqlens && eight < 2 * cus) return false;
+    if (causal && p.Nk < 4LL * p.Nq) return G % 4 == 0 && four >= 8 * cus;
     const long long rest = four % (2 * cus);
     const long long cost4 = four / (2 * cus) * 1000 + (rest == 0 ? 0 : rest <= cus ? 580 : 1000);
     return (eight + cus - 1) / cus * 955 < cost4;
