@@ -68,6 +68,7 @@ namespace {
 
 constexpr int WR = 32;        // query rows per slot
 constexpr int NSLOT = 4;      // slots per workgroup where nothing speaks for another number
+constexpr int RANKED_KEYS = 512, RANKED_KEYS_EACH = 20;   // cache from which an order by length pays: keys, keys a sequence
 constexpr float kMaxLaneSum = 4096.0f;   // largest 16-weight lane sum kept without a rescale
 
 struct PrefillArgs {
@@ -161,7 +162,13 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
     // long ones finish last (4 x 32/8 heads, 512 rows, 4096 to 1024 keys, D = 64
     // 68 -> 54; 16 such sequences 250 -> 210; 6 of 1024 rows, D = 128 288 -> 250).
     // About equal ones stay in the order of the batch, where workgroups that
-    // share a CU share its L1 as well (4 x 4096 keys 83 against 86 by rank).
+    // share a CU share its L1 as well (4 x 4096 keys 83 against 86 by rank), and
+    // so do those of short caches, where ranking (0.5 us, 1.5 for 40 and more
+    // sequences, ahead of the first load) costs more than it gives (in the
+    // order of the batch, which is by length, against ranked, D = 64: 43 x 8/8
+    // heads, 32 rows, 256 keys 9.5 / 11.0, 512 12.6 / 13.8, 1024 17.6 / 18.6, but
+    // in a random one 21.0 / 18.7; 12 x 32/4, 128 rows, 256 keys 11.9 / 12.1,
+    // 512 14.8 / 14.1).
     const int q_ = a.per_mb.div(bid);
     int mb = q_ < a.first ? a.nmb - 1 - q_ : q_ - a.first;
     int rest = bid - q_ * a.per_mb.d;
@@ -736,7 +743,8 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
     a.first = p.causal && at_once ? (cus + (int)a.per_mb.d - 1) / (int)a.per_mb.d : a.nmb;
     a.ranked = 0;
     a.row_blocks = Divisor(a.nmb);
-    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > cus) {
+    if (p.seqlens && p.B > 1 && p.B <= kMaxRanked && nblocks > cus && p.Nk >= RANKED_KEYS &&
+        p.Nk >= RANKED_KEYS_EACH * (long long)p.B) {
         const int per_seq = p.Hkv * (G / a.HW);
         a.per_seq = Divisor(per_seq);
         a.ranked = at_once ? (cus + per_seq - 1) / per_seq : a.nmb * p.B;
