@@ -169,13 +169,13 @@ __device__ __forceinline__ unsigned lds_address(void *p) {
 // assembly, with no result register, because the compiler makes every later
 // LDS read wait for such loads; nothing waits for them but lds_loads_done(),
 // which goes before the barrier that publishes the data.  base, bytes and dst
-// are wave-uniform; the s_nop covers a scalar register that a vector
-// instruction wrote just before (five wait states to its use in an address).
+// are wave-uniform; dst is an operand in m0, so that the compiler knows what m0
+// holds; the s_nop covers a scalar register that a vector instruction wrote
+// just before (five wait states to its use in an address).
 __device__ __forceinline__ void load_lds16(const void *base, int bytes, unsigned dst, int off) {
     const unsigned long long p = (unsigned long long)base;   // below 2^48: the descriptor's stride bits stay 0
     const uint4_t rsrc = {(unsigned)p, (unsigned)(p >> 32), (unsigned)bytes, 0x00020000u};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
-                 : "memory");
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(dst), "v"(off), "s"(rsrc) : "memory");
 }
 template <int N> __device__ __forceinline__ void lds_loads_done() {   // all but the last N loads of the wave
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
