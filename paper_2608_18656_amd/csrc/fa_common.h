@@ -42,11 +42,6 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// 16-bit storage word -> fp32 (exact for both formats).
-__device__ __forceinline__ float to_f32(_Float16 x) { return (float)x; }
-__device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
-__device__ __forceinline__ float to_f32(float x) { return x; }
-
 // fp32 -> output element, round to nearest even.
 template <typename T> __device__ __forceinline__ T from_f32(float x);
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
@@ -67,12 +62,9 @@ __device__ __forceinline__ float4_t mfma16(bf16x8_t a, bf16x8_t b, float4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Eight 16-bit values loaded / stored as one 16-byte word.
+// Eight 16-bit values as one 16-byte word.
 template <typename V> __device__ __forceinline__ V as_vec8(uint4_t u) {
     return __builtin_bit_cast(V, u);
-}
-template <typename V> __device__ __forceinline__ uint4_t as_u4(V v) {
-    return __builtin_bit_cast(uint4_t, v);
 }
 
 // bf16 x8 (as raw 16-byte word) -> f16 x8 (raw), round to nearest even.
@@ -86,14 +78,6 @@ __device__ __forceinline__ uint4_t bf16x8_to_f16x8(uint4_t u) {
     return __builtin_bit_cast(uint4_t, h);
 }
 
-// Two fp32 values -> packed f16 pair (first in the low half), round to nearest even.
-__device__ __forceinline__ unsigned pack_f16x2(float lo, float hi) {
-    half2_t h;
-    h[0] = (_Float16)lo;
-    h[1] = (_Float16)hi;
-    return __builtin_bit_cast(unsigned, h);
-}
-
 // Pack 8 fp32 values to f16 x8, round to nearest even.
 __device__ __forceinline__ half8_t pack_f16x8(float a0, float a1, float a2, float a3, float a4,
                                               float a5, float a6, float a7) {
@@ -101,19 +85,6 @@ __device__ __forceinline__ half8_t pack_f16x8(float a0, float a1, float a2, floa
     h[0] = (_Float16)a0; h[1] = (_Float16)a1; h[2] = (_Float16)a2; h[3] = (_Float16)a3;
     h[4] = (_Float16)a4; h[5] = (_Float16)a5; h[6] = (_Float16)a6; h[7] = (_Float16)a7;
     return h;
-}
-
-// Sum of 16 f16 values (two f16 x8 words) accumulated in fp32 (dot products
-// with (1, 1), two independent chains).
-__device__ __forceinline__ float sum_f16x16(half8_t a, half8_t b) {
-    const half2_t one = {(_Float16)1.0f, (_Float16)1.0f};
-    float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        s0 = __builtin_amdgcn_fdot2(half2_t{a[2 * i], a[2 * i + 1]}, one, s0, false);
-        s1 = __builtin_amdgcn_fdot2(half2_t{b[2 * i], b[2 * i + 1]}, one, s1, false);
-    }
-    return s0 + s1;
 }
 
 // Reductions over the lane pair (l, l^32).  v_permlane32_swap exchanges the
@@ -189,10 +160,6 @@ __device__ __forceinline__ uint4_t ld16(const void *p) {
     return *reinterpret_cast<const uint4_t *>(p);
 }
 __device__ __forceinline__ void st16(void *p, uint4_t v) { *reinterpret_cast<uint4_t *>(p) = v; }
-// Streaming 16-byte load for data read exactly once (non-temporal hint).
-__device__ __forceinline__ uint4_t ld16_stream(const void *p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const uint4_t *>(p));
-}
 
 // Division of n < 2^31 by a launch constant d >= 1 in three scalar
 // instructions (an integer division takes some twenty vector ones, which
