@@ -38,10 +38,10 @@
 // 16 columns' maxima grow in turn, cost 50 more instructions.
 // Timed in turn, before (all fp32 MFMA, copies through registers with the
 // 16-bit values widened, a rescale whenever a maximum grows) and now, in us:
-// causal bf16 16/2 heads, 1111 rows, D = 96 39 -> 21; D = 256 205 -> 43;
-// causal bf16 4 x 32/8, 2048 rows, D = 96 639 -> 223; decode bf16 16 x 32/8 x
-// 2048, D = 96 50 -> 25; causal fp32 16 heads, 777 rows, D = 64 27.5 -> 24.0,
-// D = 256 227 -> 82; fp32 2 heads, 128 rows, D = 64 7.7 -> 6.0.
+// causal bf16 16/2 heads, 1111 rows, D = 96 39 -> 21; D = 256 205 -> 40;
+// causal bf16 4 x 32/8, 2048 rows, D = 96 639 -> 222; decode bf16 16 x 32/8 x
+// 2048, D = 96 50 -> 25; causal fp32 16 heads, 777 rows, D = 64 27.5 -> 24.2,
+// D = 256 227 -> 78; fp32 2 heads, 128 rows, D = 64 7.7 -> 6.1.
 #include <type_traits>
 
 #include "fa_common.h"
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
         // lanes l and l ^ 16 have halves of an 8-column chunk in each of two
         // column tiles and exchange them, so that each stores 16 bytes (16 heads,
         // 300 rows, D = 256, bf16 16.9 -> 16.4 us; 4 x 32/8, 2048 rows, D = 96
-        // 233 -> 226; small calls +-1 %)
+        // -3 %; small calls +-1 %)
         typedef TOUT t4 __attribute__((ext_vector_type(4)));
         typedef unsigned uint2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -565,43 +565,58 @@ hipError_t launch_t(const Problem &p, hipStream_t stream) {
 // second half being short), large ones for grids that fill the card anyway.
 // In us, on both sides of each line:
 //   fp32, up to 128 columns: (1, 4) against (2, 4): 16 heads, 777 rows causal,
-//     D = 64 25.4 / 26.4; decode 16 x 32/8 x 2048, D = 64 36.6 / 47.8; past
-//     the line, 2/8 heads x 1000, D = 96 53.9 / 38.3, 4 x 32/8 x 1024 causal,
-//     D = 64 230 / 174
-//   16 bits, up to 128: (2, 4) against (4, 2): 16 x 512, D = 80 10.3 / 13.6;
-//     16/2 x 100 against 4000, D = 96 37 / 66; 32/8 x 2048 causal, D = 96
-//     95 / 63; between them, causal calls of about square shape, (2, 2) against
-//     (4, 2): 16/2 x 1111, D = 96 23.1 / 24.7; 16 x 1400, D = 80 27.6 / 30.6 (not
-//     causal, 2 x 16/2 x 600, D = 88 27.4 / 21.8)
-//   fp32, above 128: (2, 2) against (4, 2): 16 x 777 causal, D = 192 63 / 88;
-//     16 x 1024, D = 192 152 / 118
+//     D = 64 24.2 / 26.1; decode 16 x 32/8 x 2048, D = 64 36.5 / 47.5; past
+//     the line, 8/2 heads x 1000, D = 96 54.8 / 38.6, 4 x 32/8 x 1024 causal,
+//     D = 64 227 / 171
+//   16 bits, up to 128: (2, 4) against (4, 2): 16 x 512, D = 80 9.4 / 12.6;
+//     16/2 x 100 against 4000, D = 96 35 / 63; 32/8 x 2048 causal, D = 96
+//     100 / 65.  Between them, causal calls of about square shape, (2, 2) at 65
+//     to 96 columns, where three of its workgroups fit a CU and one of (2, 4):
+//     over 96 grids between the lines, D = 72 to 96, -11 to +4 % against (4, 2),
+//     slower only from 700 workgroups of many heads on (bf16, D = 80: 16/2 x 1026
+//     rows 18.7 / 19.8, x 1526 26.0 / 29.1, 32/8 x 666 14.7 / 15.8, x 758 18.3 /
+//     17.5; not causal, 2 x 16/2 x 600, D = 88 25.0 / 19.6).  Up to 64 columns the
+//     line of (2, 4) lies at twice as many workgroups, and past it (2, 2) is the
+//     slower one (16/2 x 2221, D = 56 36.5 / 31.4; 32/8 x 1108 23.1 / 19.0; D = 32,
+//     1531 rows 22.4 / 23.0, 2560 49.3 / 45.0); at 97 to 128 no grid lies between
+//   fp32, above 128: (2, 2) against (4, 2): 16 x 777 causal, D = 192 62 / 85;
+//     16 x 1024, D = 192 154 / 115; up to 160 columns, where two workgroups of (2,
+//     2) fit a CU, no grid is slower with it by more than 2 % (32/8, D = 160:
+//     causal, 1024 rows 119 / 116, 1371 199 / 214, 2080 410 / 428; not causal, 1718
+//     573 / 653)
 //   above 128, (4, 2) against (8, 1): bf16 16/2 x 1111 causal, D = 256
-//     43 / 66; with a workgroup of (8, 1) for every CU, 32/8 x 1024, D = 256
-//     81 / 70, fp32 32 x 1024, D = 192 223 / 211 (but D = 160, 2 x 32 x 1024
-//     causal 219 / 241)
+//     40 / 62; from a workgroup of (8, 1) for every CU, 32/8 x 1024, D = 256
+//     77 / 66, fp32 32 x 1024, D = 192 224 / 212.  (8, 1) gains 5 to 14 % in bf16, 3
+//     to 6 in fp32, where its rounds are full, as they are from some two rounds
+//     on; it loses where they are not (not causal, 300 to 390 workgroups, +13 to
+//     +26 %) and where a causal call's longest row block then decides (bf16, D =
+//     256, 32/8 x 1024 45.6 / 59.5, x 1371 80.6 / 77.3, x 1718 110 / 94)
+// The lines are those of a whole card, so that a call's layout, and with it the
+// order of its sums, does not go by the device's mode.
 template <typename TIN, typename TOUT, int DP>
 hipError_t launch_k(const Problem &p, hipStream_t s) {
     constexpr bool F32 = sizeof(typename Elem<TIN>::scalar) == 4, WIDE = DP > 128;
     constexpr int NB = F32 ? 1 : 2;
     const long long cols = (long long)p.Nq * (p.Hq / p.Hkv), kvheads = (long long)p.B * p.Hkv;
     auto groups = [&](int ns) { return (cols + QB * ns - 1) / (QB * ns) * kvheads; };   // workgroups of ns blocks
-    if constexpr (F32 || !WIDE) {
+    constexpr bool PAIR = F32 && WIDE && 2 * GCfg<TIN, DP, 2, 2, NB>::BYTES <= 163840;   // two workgroups of (2, 2) fit a CU
+    if constexpr (PAIR) {
+        return launch_t<TIN, TOUT, DP, 2, 2, NB>(p, s);
+    } else if constexpr (F32 || !WIDE) {
         constexpr int NS = F32 && !WIDE ? 1 : 2, KSP = WIDE ? 2 : 4;
         constexpr int FIT = 163840 / GCfg<TIN, DP, NS, KSP, NB>::BYTES;   // workgroups per CU by LDS
         const int rounds = p.causal && p.Nk < 2LL * p.Nq ? 2 : 1;
         if (groups(NS) <= CUS * (FIT < 2 ? FIT : 2) * rounds) return launch_t<TIN, TOUT, DP, NS, KSP, NB>(p, s);
-        if constexpr (!F32 && !WIDE) {   // (2, 2), where more of them than of (2, 4) start at once (96 columns)
+        if constexpr (!F32 && DP == 96) {
             constexpr int FIT2 = 163840 / GCfg<TIN, DP, 2, 2, NB>::BYTES;
-            if constexpr (FIT2 < 4 && FIT2 > 2 * FIT) {
-                if (rounds == 2 && groups(2) <= CUS * FIT2) return launch_t<TIN, TOUT, DP, 2, 2, NB>(p, s);
-            }
+            if (rounds == 2 && groups(2) <= CUS * FIT2) return launch_t<TIN, TOUT, DP, 2, 2, NB>(p, s);
         }
     }
-    if constexpr (WIDE && !(F32 && DP == 160)) {
+    if constexpr (WIDE && !PAIR) {
         if (groups(8) >= CUS) return launch_t<TIN, TOUT, DP, 8, 1, NB>(p, s);
     }
     if constexpr (F32 && !WIDE) return launch_t<TIN, TOUT, DP, 2, 4, NB>(p, s);
-    else return launch_t<TIN, TOUT, DP, 4, 2, NB>(p, s);
+    else if constexpr (!PAIR) return launch_t<TIN, TOUT, DP, 4, 2, NB>(p, s);
 }
 
 template <typename TIN, typename TOUT>

@@ -24,7 +24,8 @@ SHAPES = [
     (1, 260, 260, 70, 70, 96, True, "bf16"),
     (2, 300, 300, 17, 40, 64, False, "f32"),     # (2, 4)
     (1, 33, 33, 250, 97, 192, False, "f32"),     # (4, 2)
-    (1, 130, 130, 100, 37, 136, False, "f32"),
+    (1, 130, 130, 100, 37, 136, False, "f32"),   # (2, 2), as in every fp32 call of 129 to 160 columns
+    (1, 300, 300, 140, 150, 160, True, "f32"),
     (2, 130, 130, 17, 33, 192, False, "bf16"),   # (8, 1)
     (1, 260, 260, 129, 140, 256, True, "f16"),
     (2, 130, 130, 130, 130, 224, True, "f32"),
@@ -70,8 +71,8 @@ def test_rising_scores_and_scales(D, dtype, scale):
 
 @pytest.mark.parametrize("D,dtype", [(96, "f16"), (96, "bf16"), (160, "f16"), (64, "f32")])
 def test_tiny_weights(D, dtype):
-    """One key carries weight 1, the others 2^-45 each: an infinite value among
-    those still shows; a large one counts by its weight."""
+    """One key carries weight 1, the others 2^-46 each: an infinite value among
+    those still shows, and the one key's value counts whole."""
     dt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
     q = torch.zeros(1, 16, 1, D, dtype=dt)
     k = torch.zeros(1, 100, 1, D, dtype=dt)
