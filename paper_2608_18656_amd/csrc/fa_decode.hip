@@ -42,7 +42,7 @@ constexpr int QG = 16;         // query heads per MFMA column block
 constexpr int NW = 8;          // waves per workgroup
 constexpr float TAU = 8.0f;    // lazy-rescale threshold (log2 units)
 constexpr int MIN_KEYS_PER_SPLIT = 256;
-constexpr int CUS = 256;                 // compute units
+constexpr int CUS = 256;                 // compute units of the card
 constexpr long long LONG_SPLIT = 4096 * 100;   // keys (hundredths) beyond which one workgroup fills a CU's share of HBM
 constexpr int RANKED_KEYS = 512;         // keys per split from which an order by length pays
 constexpr int MAX_ROUNDS = 8;            // most rounds of one workgroup per CU that splitting may make
@@ -457,6 +457,15 @@ bool decode_supported(int Nq, int Hkv, int D, fa_dtype_t in) {
 // 200) and its loads (4 a split).  The model picks a count within 6 % of the
 // best of those measured (a dozen shapes from 24 to 720 units, 512 to 32768
 // keys).  At least 256 keys per split (one chunk for each wave).
+// Lengths of their own are not known here, and a call with equal ones has the
+// bits of one without, so the count is the same.  Over 640 such calls (lengths
+// down to an eighth of the cache) it gains 12 % against ceil(256 / U) splits;
+// seven are slower by more than 3 %, where D = 128 leaves 176 to 224 workgroups
+// and the longest sequences then decide (12 x 32/8, 1684 to 282 keys 15.9 ->
+// 18.3; 14 x 32/8, 4067 to 977 31.2 -> 35.7).  Over 1280 calls without lengths
+// none is.
+// CUS is the whole card's, not the device's: the count must be the same in
+// fa_workspace_bytes, which asks no device, and sums must not go by its mode.
 int decode_default_splits(int B, int Hq, int Hkv, int Nk, int D) {
     const int G = Hq / Hkv;
     const long long units = (long long)B * Hkv * ((G + QG - 1) / QG);

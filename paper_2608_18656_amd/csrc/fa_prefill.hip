@@ -520,14 +520,13 @@ __global__ __launch_bounds__((Cfg<D, NS>::NT)) __attribute__((amdgpu_waves_per_e
         }
     };
 
-    // Tile loop: one tile per step, in order -- scores, softmax, PV.  The next
-    // tile's global loads are in flight during the step, and it is written
-    // to the other LDS stage at the end of the step.  The latencies of a
-    // step are hidden by the waves of the other workgroups on the CU, whose
-    // barriers are independent of this one's.
-    // Tile i + AHEAD is loaded during step i.  Two steps ahead, its bf16 V goes
-    // to its stage in step i + 1, before the next loads; one step ahead, at the
-    // end of step i.
+    // Tile loop: one tile per step, in order -- scores, softmax, PV -- and one
+    // barrier.  The latencies of a step are hidden by the waves of the other
+    // workgroups on the CU, whose barriers are independent of this one's.
+    // Tile i + AHEAD is loaded during step i, into the stage that tile i - 1
+    // (two stages: the other one) has left.  With three stages the loads have
+    // the whole next step as well: step i waits for tile i + 1's, and writes its
+    // bf16 V, after its own scores.  With two, at its end.
     constexpr int AHEAD = SM::AHEAD;
     if (ntiles > 0) {
         vregs_t v0;
