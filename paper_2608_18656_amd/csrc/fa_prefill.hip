@@ -673,27 +673,38 @@ int default_heads(int slots, int G) {
 // Whether a D = 64 call takes eight slots per workgroup (one 16-wave workgroup
 // per CU) where the caller leaves the choice, rather than four (two of 8
 // waves).  Eight stage each tile half as often and run a full CU 4 to 5 %
-// faster; four end more evenly.  Calls whose workgroups all take about the same
-// time, not causal or few rows against many keys, compare rounds: a last round
-// that leaves four-slot workgroups alone on their CUs costs them 0.58 of a full
-// one (4 against 8, us, 32/8 heads, bf16: 1056 rows 24.8 / 23.3; 1400 rows
-// 28.9 / 26.9; 2048 rows 47.9 / 45.6; 2500 rows 77.8 / 92.9; 5920 rows 342.9 /
-// 329.6; 8192 rows 631 / 605; 16/1 heads, 3000 rows 54.0 / 48.1; fp16, 16384 rows
-// 1245 / 1198; bf16, 9000 rows 417.6 / 453.7; causal, 4 x 1024 rows against 4096
-// keys 141.7 / 134.2, 5 x 1000 against 5000 216 / 228).  Square causal calls
-// end on short workgroups in any case: eight from four full rounds on, where
-// four heads share a workgroup (32/8, 8192 rows 329 / 320; 16/1, 16384 rows,
-// fp16 628 / 621; but 6000 rows 185 / 189, and 2 x 16/16 heads, 5000 rows 137 /
-// 146).  Lengths of their own are not known here.  Where they are equal, eight
-// gain as much (16 x 32/8 heads, 512 rows against 4096 keys 370 / 348; 32 x 16/2,
-// 256 rows 205 / 184), and long uneven ones lose at most 1 % (the first call
-// with 614 keys and more 180 / 181); short ones would lose up to 12 % (16 x 512
-// rows against up to 1024 keys 64.5 / 72.5, against 2048 99.8 / 104.1, where
-// equal ones gain 1.4 %), and so would those of one round, whose long and short
-// workgroups then no longer share CUs (4 x 512 rows against 2048 to 4096 keys
-// 62.7 / 69.2): eight from 2048 keys and two rounds on.
+// faster; four end more evenly, and one's start and end go under in the other's
+// steps.  Calls whose workgroups all take about the same time, not causal or few
+// rows against many keys, compare rounds: a last round that leaves four-slot
+// workgroups alone on their CUs costs them 0.58 of a full one (4 against 8, us,
+// 32/8 heads, bf16: 1056 rows 24.8 / 23.3; 1400 rows 28.9 / 26.9; 2048 rows 47.9 /
+// 45.6; 2500 rows 77.8 / 92.9; 5920 rows 342.9 / 329.6; 8192 rows 631 / 605; 16/1
+// heads, 3000 rows 54.0 / 48.1; fp16, 16384 rows 1245 / 1198; bf16, 9000 rows 417.6
+// / 453.7; causal, 4 x 1024 rows against 4096 keys 141.7 / 134.2, 5 x 1000 against
+// 5000 216 / 228), and a round's start and end cost eight the time of some 90
+// keys more, 32 where there is one round (over 1600 calls of 16 to 6000 keys the
+// choice is on average 0.1 % off the better one; without those keys 2.1, at most
+// 42: 49 x 32/8, 57 rows 13.7 / 15.4; 62 x 32/8, 189 rows 47.7 / 63.7; 14 x 32/4,
+// 67 rows 8.5 / 10.0; 7 x 32/8, 1406 rows 143.9 / 153.7).  A K/V that the memory
+// side's 256 MB do not hold comes from HBM for every workgroup that reads it:
+// eight where they are half as many, and two rounds or more (97 x 16/16 heads,
+// 172 rows, 2228 keys 401 / 322; 84 x 16/16, 506 rows, 1233 keys 419 / 338; at 290
+// to 330 MB -10 to +9 %; not for uneven lengths in order, 33 x 16/16, 439 rows,
+// 2978 to 2233 keys 223 / 256).
+// Square causal calls end on short workgroups in any case: eight from four full
+// rounds and 7168 rows on, where four heads share a workgroup (32/8, 8192 rows
+// 314 / 307; 2 x 32/8, 7200 rows 483 / 476; 16/1 16384, fp16 628 / 621; but 2 x
+// 32/8, 4700 rows 220 / 228; 29 x 32/4, 290 rows 35.7 / 46.2; and 2 x 16/16 heads,
+// 5000 rows 137 / 146).  Lengths of their own are not known here.  Where they are
+// equal, eight gain as much (16 x 32/8 heads, 512 rows against 4096 keys 370 /
+// 348; 32 x 16/2, 256 rows 205 / 184), and long uneven ones lose at most 1 % (the
+// first call with 614 keys and more 180 / 181); short ones would lose up to 12 %
+// (16 x 512 rows against up to 1024 keys 64.5 / 72.5, against 2048 99.8 / 104.1,
+// where equal ones gain 1.4 %), and so would those of one round, whose long and
+// short workgroups then no longer share CUs (4 x 512 rows against 2048 to 4096
+// keys 62.7 / 69.2): eight from 2048 keys and two rounds on.
 bool eight_slots(const Problem &p, bool causal) {
-    if (p.D != 64 || p.hw > 0 || p.block_table || (p.seqlens && p.Nk < 2048)) return false;
+    if (p.D != 64 || p.hw > 0 || p.block_table) return false;
     const long long cus = cu_count();
     if (cus == 0) return false;
     const int G = p.Hq / p.Hkv;
@@ -702,11 +713,15 @@ bool eight_slots(const Problem &p, bool causal) {
         return ((long long)p.Nq + rows - 1) / rows * p.B * p.Hkv * (G / hw);
     };
     const long long four = groups(4), eight = groups(8);
-    if (p.seqlens && eight < 2 * cus) return false;
-    if (causal && p.Nk < 4LL * p.Nq) return G % 4 == 0 && four >= 8 * cus;
+    const bool square = causal && p.Nk < 4LL * p.Nq;
+    const long long kv_bytes = 256LL * p.B * p.Hkv * p.Nk;
+    if (!square && eight >= 2 * cus && four == 2 * eight && kv_bytes > 335000000 && (!p.seqlens || p.B > kMaxRanked))
+        return true;
+    if (p.seqlens && (p.Nk < 2048 || eight < 2 * cus)) return false;
+    if (square) return G % 4 == 0 && four >= 8 * cus && p.Nk >= 7168;
     const long long rest = four % (2 * cus);
     const long long cost4 = four / (2 * cus) * 1000 + (rest == 0 ? 0 : rest <= cus ? 580 : 1000);
-    return (eight + cus - 1) / cus * 955 < cost4;
+    return (eight + cus - 1) / cus * (955 + 1000 * (eight <= cus ? 32 : 90) / p.Nk) < cost4;
 }
 
 template <typename TIN, typename TOUT, int D, int NS, bool CAUSAL>
