@@ -179,9 +179,14 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
     constexpr int NSUM = !F32 ? 1 : DP <= 64 ? 2 : 4;
     // The base of a column's weights moves (and its sums are rescaled) only
     // when a score exceeds the largest one of that time by more than GROWTH.
-    // That one then weighs 2^HEADROOM, so weights are at most 1 (a weight times
-    // any value stays in range), in fp16 2^15, for the range of their terms.
-    constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : -GROWTH;
+    // That one then weighs 2^HEADROOM; weights reach 2^(HEADROOM + GROWTH), in
+    // fp16 2^15, for the range of their terms.  Otherwise the value products take
+    // SHARE of them (exact), so that a weight times any value stays in range; a
+    // base higher by GROWTH would do that as well, but exponents further from 0
+    // are rounded more coarsely (error against fp64, 16 heads, 777 rows, D = 64,
+    // fp32 1.87e-7 -> 1.98e-7, 16/2, 1111 rows, D = 96, bf16 1.33e-7 -> 1.50e-7;
+    // the multiplications take -1 to +1 %, bf16 at D = 256 1 to 4).
+    constexpr float GROWTH = 4.f, HEADROOM = F16 ? 15.f - GROWTH : 0.f, SHARE = F16 ? 1.f : 0x1p-4f;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[SM::BYTES];
 
     const int tid = threadIdx.x, l = tid & 63;
@@ -385,6 +390,10 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
         for (int j = 0; j < NB; ++j) lsum += (p[4 * j] + p[4 * j + 1]) + (p[4 * j + 2] + p[4 * j + 3]);
 
         // ---- values
+        if constexpr (!F16) {
+#pragma unroll
+            for (int i = 0; i < 4 * NB; ++i) p[i] *= SHARE;
+        }
         if constexpr (F32) {
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -496,7 +505,7 @@ __global__ __launch_bounds__(64 * NSLOT * KSP) __attribute__((amdgpu_waves_per_e
     }
     lsum = pair_sum(half_sum(lsum));
     if (!valid) return;
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;   // no visible key: 0
+    const float inv = lsum > 0.f ? (1.f / SHARE) / lsum : 0.f;   // no visible key: 0
     TOUT *op = reinterpret_cast<TOUT *>(a.o) + ((size_t)((size_t)b * Nq + row) * a.Hq + h) * D;
     if constexpr (sizeof(TOUT) == 4) {
 #pragma unroll
