@@ -160,7 +160,7 @@ fa_status_t fa_fwd_packed(const void *q, const void *k, const void *v, void *o, 
  * one load of a key/value row serving several query heads), and
  * heads_per_workgroup of them are different query heads of the group (the
  * rest consecutive row blocks).  slots_per_workgroup: 0 (what fa_fwd uses: 4,
- * or 8 for some large grids at D = 64), 1 (no sharing: every slot stages its
+ * or 8 for some grids at D = 64), 1 (no sharing: every slot stages its
  * own tiles), 2, 4 or 8;
  * heads_per_workgroup: 0 (the most heads, up to 4, that divide both the slots
  * and Hq / Hkv), 1, 2, 4 or 8, dividing Hq / Hkv and the slots.  The result
