@@ -305,15 +305,17 @@ __global__ __launch_bounds__(64 * NW, 1) void decode_split_kernel(DecodeArgs a) 
         const size_t bh = (size_t)b * a.Hq + g * G + mh;
         const bool direct = a.S.d == 1;   // one split: the result itself
         const size_t slot = bh * a.S.d + s;   // (bh itself with one split)
-        // a sequence with no valid key (per-sequence lengths) gives 0 and -inf
-        const float inv = direct ? (L > 0.f ? 1.f / L : 0.f) : 1.f;
+        // as the merge does: a sequence with no valid key (per-sequence lengths),
+        // or whose scores are not numbers, gives 0 and -inf
+        const bool some = !direct || L > 0.f;
+        const float inv = direct ? 1.f / L : 1.f;
         float acc[D / 16];
 #pragma unroll
         for (int j = 0; j < D / 16; ++j) {
             acc[j] = 0.f;
 #pragma unroll
             for (int ww = 0; ww < NW; ++ww) acc[j] += wgt[ww] * mf[(ww * QG + mq) * (D + 2) + part + 16 * j];
-            acc[j] *= inv;
+            acc[j] = some ? acc[j] * inv : 0.f;
         }
         if (!direct || a.out_f32) {
             float *op = (direct ? reinterpret_cast<float *>(a.o) : a.opart) + slot * D + part;
@@ -379,7 +381,8 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(const float *__restri
         }
         M = Mc;
     }
-    // a sequence with no valid key (per-sequence lengths) gives 0 and -inf
+    // a sequence with no valid key (per-sequence lengths), or whose scores are not
+    // numbers, gives 0 and -inf
     reinterpret_cast<TOUT *>(o)[(size_t)bh * D + t] = from_f32<TOUT>(L > 0.f ? acc / L : 0.f);
     if (lse && t == 0) lse[bh] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
 }

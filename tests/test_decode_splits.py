@@ -74,3 +74,19 @@ def test_lengths_spread_over_the_splits(D, dtype, page, Nk):
             pools.append(pool)
         op, lp = fa.fwd_kvcache_paged(q.cuda(), *pools, order.view(B, -1), sl, scale=scale, out_dtype=torch.float32)
         assert torch.equal(op, o) and torch.equal(lp, lse)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,dtype", [(64, "bf16"), (64, "f16"), (128, "bf16"), (128, "f16")])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_scores_that_are_no_numbers(D, dtype, bad):
+    """One split writes its own result: the same as the merge of several, 0 and -inf."""
+    q, k, v = (t.cuda() for t in make_qkv(2, 6, 2, 1, 600, D, dtype, seed=D))
+    q[0, 0, 1, 0], q[0, 0, 4, 0] = abs(q[0, 0, 1, 0]) + 1, abs(q[0, 0, 4, 0]) + 1
+    k[0, 100, :, 0] = bad
+    res = [fa.fwd(q, k, v, num_splits=S, scale=default_scale(D)) for S in (1, 3)]
+    for o, lse in res:
+        for h in (1, 4):
+            assert torch.all(o[0, 0, h] == 0) and lse[0, h, 0] == -float("inf")
+    assert not res[0][0].isnan().any() and torch.equal(res[0][1].isinf(), res[1][1].isinf())
+    assert torch.equal(res[0][0] == 0, res[1][0] == 0)
